@@ -143,14 +143,19 @@ def sources_digest():
 
 def kernel_key(profiler_name):
     """The library's timing name of a kernel from the demangled name rocprofv3
-    prints (fit_hist_kernel<T, EPT, kLinear, kLat, kGlobal> ->
-    fit_hist_kernel<T,EPT,mode[,rebuilt]>; fit_small_kernel<d>)."""
+    prints (fit_hist_kernel<T, EPT, mode, levels> -> fit_hist_kernel<T,EPT,mode>;
+    fit_small_kernel<d>; and, in traces of earlier builds,
+    fit_hist_kernel<T, EPT, kLinear, kLat, kGlobal>)."""
     m = re.search(r"fit_hist_kernel<(\d+), (\d+), (true|false), (true|false), (true|false)>",
                   profiler_name)
     if m:
         mode = "lattice" if m.group(4) == "true" else "linear" if m.group(3) == "true" else "grid"
         rebuilt = ",rebuilt" if m.group(5) == "true" else ""
         return f"fit_hist_kernel<{m.group(1)},{m.group(2)},{mode}{rebuilt}>"
+    m = re.search(r"fit_hist_kernel<(\d+), (\d+), (\d), (\d+)>", profiler_name)   # T, EPT, mode, levels
+    if m:
+        mode = ("lattice", "linear", "wide", "grid")[int(m.group(3))]
+        return f"fit_hist_kernel<{m.group(1)},{m.group(2)},{mode}>"
     m = re.search(r"fit_small_kernel<(\d+)>", profiler_name)
     if m:
         return f"fit_small_kernel<{m.group(1)}>"

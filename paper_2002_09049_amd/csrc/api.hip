@@ -327,10 +327,17 @@ std::vector<FitJob> build_fit_jobs(Search mode, bool hist_fits, const mpq_layer 
                   (L.d <= mpq::kSmallMaxDim ? (double)L.d * (double)n_grid / 24.0 : (double)(L.d + n_grid));
         j.layers.push_back(l);
     };
+    // a call whose channels would leave half of the 1024 SIMDs without a
+    // wavefront gives each channel four (256 x 1152 on a caller's grid: 71 us
+    // against 145 us with one)
+    int64_t waves = 0;
+    for (int l = 0; l < n_layers; ++l)
+        if (layers[l].c_out > 0 && hist(layers[l])) waves += layers[l].c_out * mpq::hist_waves(layers[l].d);
+    const bool wide = waves <= 512;
     for (int l = 0; l < n_layers; ++l) {
         const mpq_layer &L = layers[l];
         if (L.c_out == 0 || !hist(L) || !own(L)) continue;
-        FitJob j = fresh(mpq::hist_variant(L.d));
+        FitJob j = fresh(mpq::hist_variant(L.d, wide));
         add_layer(j, l);
         jobs.push_back(j);
     }
@@ -345,7 +352,7 @@ std::vector<FitJob> build_fit_jobs(Search mode, bool hist_fits, const mpq_layer 
             }
             if (l == n_layers) break;
             const mpq_layer &L = layers[l];
-            if (L.c_out == 0 || !hist(L) || own(L) || mpq::hist_variant(L.d) != v) continue;
+            if (L.c_out == 0 || !hist(L) || own(L) || mpq::hist_variant(L.d, wide) != v) continue;
             add_layer(j, l);
         }
     }
@@ -742,7 +749,7 @@ void quantize_link_d(QuantizeStep *q)
     std::vector<int> d_grp(q->err.size());
     mpq::err_item_d_offsets(q->err.data(), (int)q->err.size(), d_off.data(), d_grp.data());
     for (FitJob &j : q->jobs) {
-        if (j.dense || !mpq::hist_variant_writes_d(j.variant)) continue;
+        if (j.dense) continue;
         for (int i = 0; i < j.b.n_layers; ++i) {
             const int e = q->err_of[j.layers[i]];
             if (e < 0 || d_off[e] < 0) continue;

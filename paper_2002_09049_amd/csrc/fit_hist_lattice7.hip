@@ -1,0 +1,23 @@
+// The lattice mode of the histogram search with 7 levels (fit_hist_kernel.hpp), for every
+// variant of kVariants (fit_hist.hip) that takes it.
+#include "fit_hist_kernel.hpp"
+
+namespace mpq {
+
+hipError_t launch_hist_lattice7(const HistBatch &b, int T, int ept, int64_t channels, hipStream_t s)
+{
+    if (T == 64 && ept == 20) return launch_hist_t<64, 20, kHistLattice, 7>(b, channels, s);
+    if (T == 128 && ept == 20) return launch_hist_t<128, 20, kHistLattice, 7>(b, channels, s);
+    if (T == 128 && ept == 36) return launch_hist_t<128, 36, kHistLattice, 7>(b, channels, s);
+    if (T == 256 && ept == 36) return launch_hist_t<256, 36, kHistLattice, 7>(b, channels, s);
+    if (T == 512 && ept == 32) return launch_hist_t<512, 32, kHistLattice, 7>(b, channels, s);
+    if (T == 512 && ept == 52) return launch_hist_t<512, 52, kHistLattice, 7>(b, channels, s);
+    if (T == 512 && ept == 64) return launch_hist_t<512, 64, kHistLattice, 7>(b, channels, s);
+    if (T == 256 && ept == 4) return launch_hist_t<256, 4, kHistLattice, 7>(b, channels, s);
+    if (T == 256 && ept == 8) return launch_hist_t<256, 8, kHistLattice, 7>(b, channels, s);
+    if (T == 256 && ept == 12) return launch_hist_t<256, 12, kHistLattice, 7>(b, channels, s);
+    if (T == 256 && ept == 20) return launch_hist_t<256, 20, kHistLattice, 7>(b, channels, s);
+    return hipErrorInvalidValue;
+}
+
+}  // namespace mpq

@@ -91,7 +91,7 @@ struct HistBatch {
     int M, P, G;
     const float *grid;  // device multipliers or nullptr (default grid)
     double tol;
-    int nlat;           // lattice buckets ((2M-1) G + 1) or 0; set by launch_fit_hist
+    int points;         // lattice mode's distinct boundary points; set by launch_fit_hist
     // Points already stored per channel (start = s >= 1: only the channels
     // whose count is s take part; their residual is rebuilt from the stored
     // points).  single == 0: the fit runs to its end with the stopping rule
@@ -117,9 +117,11 @@ static_assert(sizeof(HistBatch) <= 4096, "kernel arguments");
 
 size_t fit_hist_lds(int G);
 bool fit_hist_supports(int64_t d);
-int hist_variant(int64_t d);   // layers with equal variants may share a launch
+// Layers with equal variants may share a launch.  wide: the variants of four
+// wavefronts per channel where they exist (same results).
+int hist_variant(int64_t d, bool wide);
+int hist_waves(int64_t d);     // wavefronts per channel of the others
 int hist_variant_count();      // variants are 0 .. hist_variant_count() - 1
-bool hist_variant_writes_d(int v);   // the variant's fit fills HistLayer::dres
 // Channels of up to kSmallMaxDim weights take the short-channel variants
 // (fit_small.hip), one per length d: one wavefront per channel, lanes over
 // the candidates, evaluated directly; the same batch descriptors and
@@ -131,6 +133,17 @@ std::string fit_small_name(int d);
 // when default_grid, else a caller's grid), as LaunchTimer records it.
 std::string hist_kernel_name(int64_t d, int M, int G, bool default_grid);
 hipError_t launch_fit_hist(const HistBatch &b, int variant, int64_t channels, hipStream_t s);
+// Its modes (fit_hist_kernel.hpp; the number is the levels M), the variant by
+// threads and elements per thread.
+hipError_t launch_hist_lattice1(const HistBatch &b, int T, int ept, int64_t channels, hipStream_t s);
+hipError_t launch_hist_lattice3(const HistBatch &b, int T, int ept, int64_t channels, hipStream_t s);
+hipError_t launch_hist_lattice7(const HistBatch &b, int T, int ept, int64_t channels, hipStream_t s);
+hipError_t launch_hist_lattice15(const HistBatch &b, int T, int ept, int64_t channels, hipStream_t s);
+hipError_t launch_hist_linear1(const HistBatch &b, int T, int ept, int64_t channels, hipStream_t s);
+hipError_t launch_hist_linear3(const HistBatch &b, int T, int ept, int64_t channels, hipStream_t s);
+hipError_t launch_hist_linear7(const HistBatch &b, int T, int ept, int64_t channels, hipStream_t s);
+hipError_t launch_hist_wide(const HistBatch &b, int T, int ept, int64_t channels, hipStream_t s);
+hipError_t launch_hist_grid(const HistBatch &b, int T, int ept, int64_t channels, hipStream_t s);
 // The paper's own grid (Eq. (11), Def. 1): one workgroup of 256 threads per
 // channel, channels of up to kPaperMaxDim weights, the layer descriptors of
 // the histogram search (HistLayer; the calibration fields unused).

@@ -2,11 +2,11 @@
 //
 // Within a wavefront the exchange steps are, in order: DPP quad_perm
 // [1,0,3,2] and [2,3,0,1], DPP row_half_mirror, DPP row_mirror (these
-// combine lanes within a row of 16), ds_swizzle with xor mask 16 (combines
-// the two rows of each half-wave) and finally a readlane of lanes 0 and 32.
-// Every step combines a lane with a partner holding the other half of its
-// group, so with a commutative, associative combine every lane of a group
-// ends with the same value; the result is uniform across the wavefront.
+// combine lanes within a row of 16), v_permlane16_swap (combines the two rows
+// of each half-wave) and v_permlane32_swap (the two halves).  No step goes
+// through LDS.  Every step combines a lane with a partner holding the other
+// half of its group, so with a commutative, associative combine every lane
+// ends with the same value.
 // Across wavefronts the per-wave results go through LDS and every thread
 // combines them in wave order, so the result is deterministic.
 #pragma once
@@ -41,21 +41,14 @@ __device__ __forceinline__ uint32_t dpp(uint32_t v)
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kCtrl, 0xF, 0xF, true);
 }
 
-__device__ __forceinline__ uint32_t swizzle_xor16(uint32_t v)
-{
-    // bitmask mode: and_mask = 0x1f, or_mask = 0, xor_mask = 0x10
-    return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, 0x401F);
-}
-
-// exchange step s (0..4) of a 32-bit value
+// exchange step s (0..3) of a 32-bit value
 template <int kStep>
 __device__ __forceinline__ uint32_t xstep(uint32_t v)
 {
     if constexpr (kStep == 0) return dpp<0xB1>(v);   // quad_perm [1,0,3,2]
     else if constexpr (kStep == 1) return dpp<0x4E>(v);  // quad_perm [2,3,0,1]
     else if constexpr (kStep == 2) return dpp<0x141>(v); // row_half_mirror
-    else if constexpr (kStep == 3) return dpp<0x140>(v); // row_mirror
-    else return swizzle_xor16(v);
+    else return dpp<0x140>(v);                            // row_mirror
 }
 
 template <int kStep>
@@ -76,6 +69,49 @@ template <int kStep>
 __device__ __forceinline__ int xstep(int v)
 {
     return (int)xstep<kStep>((uint32_t)v);
+}
+
+// Swap steps: a and b hold, in every lane, the value of the lane's own row
+// pair (half-wave pair for k32) in row order: a the even row's, b the odd
+// row's (the lower half's, the upper half's).
+template <bool k32>
+__device__ __forceinline__ void swap_step(uint32_t v, uint32_t &a, uint32_t &b)
+{
+    if constexpr (k32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        a = r[0];
+        b = r[1];
+    } else {
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        a = r[0];
+        b = r[1];
+    }
+}
+template <bool k32>
+__device__ __forceinline__ void swap_step(int v, int &a, int &b)
+{
+    uint32_t x, y;
+    swap_step<k32>((uint32_t)v, x, y);
+    a = (int)x;
+    b = (int)y;
+}
+template <bool k32>
+__device__ __forceinline__ void swap_step(float v, float &a, float &b)
+{
+    uint32_t x, y;
+    swap_step<k32>(__float_as_uint(v), x, y);
+    a = __uint_as_float(x);
+    b = __uint_as_float(y);
+}
+template <bool k32>
+__device__ __forceinline__ void swap_step(double v, double &a, double &b)
+{
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    uint32_t al, bl, ah, bh;
+    swap_step<k32>((uint32_t)u, al, bl);
+    swap_step<k32>((uint32_t)(u >> 32), ah, bh);
+    a = __longlong_as_double((long long)(((uint64_t)ah << 32) | al));
+    b = __longlong_as_double((long long)(((uint64_t)bh << 32) | bl));
 }
 
 __device__ __forceinline__ float readlane(float v, int l)
@@ -109,25 +145,19 @@ struct SumOp {
     __device__ __forceinline__ T operator()(T a, T b) const { return a + b; }
 };
 
-// Reduction over the 32 lanes of each half-wave: every lane ends with its
-// half's result.
+// Reduction over the whole wavefront; every lane ends with the result.
 template <typename T, typename Op>
-__device__ __forceinline__ T half_wave_reduce(T v, Op op)
+__device__ __forceinline__ T wave_reduce(T v, Op op)
 {
     v = op(v, xstep<0>(v));
     v = op(v, xstep<1>(v));
     v = op(v, xstep<2>(v));
     v = op(v, xstep<3>(v));
-    v = op(v, xstep<4>(v));
-    return v;
-}
-
-// Reduction over the whole wavefront; the result is wave-uniform.
-template <typename T, typename Op>
-__device__ __forceinline__ T wave_reduce(T v, Op op)
-{
-    v = half_wave_reduce(v, op);
-    return op(readlane(v, 0), readlane(v, 32));
+    T a, b;
+    swap_step<false>(v, a, b);
+    v = op(a, b);
+    swap_step<true>(v, a, b);
+    return op(a, b);
 }
 
 // Lexicographic (value, index) minimum: the smaller value, then the smaller
@@ -154,10 +184,13 @@ __device__ __forceinline__ ArgMin wave_argmin(ArgMin v)
     v = argmin_combine(v, xstep<1>(v));
     v = argmin_combine(v, xstep<2>(v));
     v = argmin_combine(v, xstep<3>(v));
-    v = argmin_combine(v, xstep<4>(v));
-    ArgMin lo{readlane(v.e, 0), readlane(v.g, 0)};
-    ArgMin hi{readlane(v.e, 32), readlane(v.g, 32)};
-    return argmin_combine(lo, hi);
+    ArgMin a, b;
+    swap_step<false>(v.e, a.e, b.e);
+    swap_step<false>(v.g, a.g, b.g);
+    v = argmin_combine(a, b);
+    swap_step<true>(v.e, a.e, b.e);
+    swap_step<true>(v.g, a.g, b.g);
+    return argmin_combine(a, b);
 }
 
 // Inclusive prefix sum over the 64 lanes (lane 0 first), DPP only:
@@ -226,10 +259,8 @@ __device__ __forceinline__ void block_max_sum(float &vmax, double &vsum, float *
                                               double *scratch_d)
 {
     constexpr int kWaves = kThreads / kWave;
-    vmax = half_wave_reduce(vmax, MaxOp());
-    vsum = half_wave_reduce(vsum, SumOp());
-    vmax = MaxOp()(readlane(vmax, 0), readlane(vmax, 32));
-    vsum = SumOp()(readlane(vsum, 0), readlane(vsum, 32));
+    vmax = wave_reduce(vmax, MaxOp());
+    vsum = wave_reduce(vsum, SumOp());
     if constexpr (kWaves > 1) {
         const int wid = threadIdx.x / kWave;
         if ((threadIdx.x % kWave) == 0) {
