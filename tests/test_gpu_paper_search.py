@@ -1,0 +1,43 @@
+"""The paper's grid where the search's range of scales can go wrong: one level
+to 127, grids of a few points (a large eta against the weights), equal
+magnitudes (no gap), lone large and sparse weights (bimodal errors), lengths at
+powers of two, in lockstep against the oracle (the call takes eta in fp32: the
+values here are fp32 values)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from gpu_util import say   # noqa: E402
+from test_gpu_variants import _fit_paper, _ok   # noqa: E402
+
+
+@pytest.fixture(scope="module")
+def orc():
+    import oracle
+    oracle.build()
+    return oracle
+
+
+def _rows(d, seed):
+    rng = np.random.default_rng(seed)
+    W = rng.standard_normal((8, d)).astype(np.float32)
+    W[1] = np.float32(0.75) * rng.choice([-1, 1], d)          # one magnitude
+    W[2, rng.random(d) < 0.9] = 0.0                             # sparse
+    W[3] *= np.float32(0.01)
+    W[3, d // 2] = 5.0                                          # a lone large weight
+    W[4] = rng.integers(-3, 4, d)                               # many equal magnitudes
+    W[5] *= np.float32(2.0 ** -12)                              # below eta
+    W[6] = 0.0
+    W[7] = np.where(np.arange(d) % 2, W[7], W[7] * np.float32(64.0))   # two scales
+    return W
+
+
+@pytest.mark.parametrize("d", [1, 2, 63, 64, 65, 128, 300, 513])
+@pytest.mark.parametrize("bits,eta", [(2, 2.0 ** -10), (3, 0.5), (4, 2.0 ** -10), (4, 0.3125), (5, 2.0 ** -6), (8, 2.0 ** -10)])
+def test_range_search(orc, d, bits, eta):
+    if bits == 8 and d > 128:
+        pytest.skip("the oracle's exact search costs O(d^2 M)")
+    say(f"case paper search d={d} bits={bits} eta={eta}")
+    W = _rows(d, 10 * d + bits)
+    _ok(orc.verify_paper(W, bits, 3, 0.0, *_fit_paper(W, bits, 3, 0.0, eta), eta=eta))
