@@ -29,8 +29,8 @@ An untimed profile step first times every kernel launch by HIP events that
 the library records on the launch's own stream (mpq_timing_enable); the
 timed steps then carry events around the error GEMM's launches only.
 `roofline` is the error GEMM (the path's one dense contraction: fp32 products
-of Eq. (12) from six bf16 piece products each, on bf16 MFMA), timed in the
-timed steps, against the dense bf16 MFMA peak; `kernels` lists every kernel.  The fit kernels'
+of Eq. (12) from four fp16 piece products each, or six bf16 ones for rows of
+less than 128, on MFMA), timed in the timed steps, against the dense 16-bit MFMA peak; `kernels` lists every kernel.  The fit kernels'
 `dense_equivalent_tflops` prices their candidate search at 7 FLOP per
 (element, candidate) pair, the work a dense evaluation of Eq. (9) does; the
 histogram search does O(d M + G) per step instead, so that figure is not an
@@ -53,8 +53,13 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_HBM_GBS = 8000.0
-PEAK_MFMA_BF16_TFLOPS = 2500.0          # dense bf16 MFMA
-GEMM_PIECE_PRODUCTS = 6                 # bf16 products per fp32 product of the error GEMM
+PEAK_MFMA_BF16_TFLOPS = 2500.0          # dense bf16 and fp16 MFMA
+
+
+def piece_products(d):
+    """16-bit products per fp32 product of the error GEMM on rows of d: four of fp16 pieces (a calibration
+    batch of moderate range, as the workloads' are), six of bf16 ones for short rows."""
+    return 4 if d >= 128 else 6
 PEAK_VALU_F32_TFLOPS = 157.3            # published (packed) FP32 vector peak
 PEAK_MFMA_I8_TOPS = 5000.0              # dense int8 MFMA
 PEAK_VALU_F32_NONPACKED_TFLOPS = 78.6   # 256 CU x 64 lanes x 2 FLOP x 2.4 GHz
@@ -64,7 +69,7 @@ PROFILES = os.path.join(ROOT, "profiles")
 ROOFLINE_KERNEL = "gemm_err_kernel"
 COPY_BYTES = 256 << 20
 STAGES = (("fit", ("fit_hist_kernel", "fit_small_kernel", "fit_dense_kernel")),
-          ("output_error", ("form_d_kernel", "gemm_err_kernel", "finish_err_kernel")),
+          ("output_error", ("scan_x_kernel", "form_d_kernel", "gemm_err_kernel", "finish_err_kernel")),
           ("reconstruct", ("reconstruct_kernel",)),
           ("deploy", ("int_forward_kernel", "integer_scales_kernel")))
 
@@ -362,8 +367,8 @@ def summarize_benches(paths):
              "Strides: " + ", ".join(f"{b['config']['workload']} {_stride_of(b)}" for b in rows)
              + f"; {rows[0]['steps'] if rows else 0} timed steps after {rows[0]['warmup'] if rows else 0} "
                "warm-up steps.",
-             "The roofline kernel is the error GEMM (6 x 2 C d n bf16 FLOP per layer against the dense bf16",
-             "MFMA peak; fp32 equivalent: 2 C d n; event-timed in the timed steps);",
+             "The roofline kernel is the error GEMM (4 x 2 C d n fp16 FLOP per layer, rows under 128 6 x bf16,",
+             "against the dense 16-bit MFMA peak; fp32 equivalent: 2 C d n; event-timed in the timed steps);",
              "the other kernels are timed in the untimed profile step, where the fit launches share the",
              "device (so a fit's duration includes its neighbours).  `search` is the fit kernel with the",
              "most time per step; its SIMD VALU busy share (the share of the SIMDs' VALU issue capacity it",
@@ -584,7 +589,7 @@ def main():
             code_reads = int((cnt * (cnt - 1) // 2).sum())
             searched = n - int((cnt > 0).sum()) if args.clip else n
             add(fk, evals=searched * wk.n_grid * d, bytes=4 * n * d + code_reads * d + n * d)
-            add("gemm_err_kernel", flop=2 * (n + C) * d * N)
+            add("gemm_err_kernel", flop=2 * (n + C) * d * N, mfma=piece_products(d) * 2 * (n + C) * d * N)
             add("form_d_kernel", bytes=8 * (n + C) * d + (n + code_reads) * d)
         else:
             # fit: G candidate errors per (element, point); reads W once, writes the codes
@@ -594,13 +599,14 @@ def main():
             searched = n - int((cnt > 0).sum()) if args.clip else n
             fit_writes_d = not separate and not args.dense
             add(fk, evals=searched * wk.n_grid * d, bytes=4 * C * d + n * d + (4 * C * d if fit_writes_d else 0))
-            add("gemm_err_kernel", flop=2 * C * d * N)
+            add("gemm_err_kernel", flop=2 * C * d * N, mfma=piece_products(d) * 2 * C * d * N)
             # form: reads W and the codes of the used points, writes D
             if not fit_writes_d:
                 add("form_d_kernel", bytes=4 * C * d + n * d + 4 * C * d)
         if args.clip:
             # the clipping pass: output errors of C * GC candidate rows
-            add("gemm_err_kernel", flop=2 * C * args.clip * d * N)
+            add("gemm_err_kernel", flop=2 * C * args.clip * d * N,
+                mfma=piece_products(d) * 2 * C * args.clip * d * N)
             add("form_d_kernel", bytes=4 * C * d + 4 * C * args.clip * d)
         # reconstruct: reads the codes of the used points, writes fp32
         add("reconstruct_kernel", bytes=n * d + 4 * C * d)
@@ -629,9 +635,9 @@ def main():
                           "hbm_gbs_algorithmic": w["bytes"] / lps / avg_s / 1e9,
                           "hbm_frac_algorithmic": w["bytes"] / lps / avg_s / 1e9 / PEAK_HBM_GBS})
             elif "flop" in w:
-                # w["flop"]: 2 C d n, the fp32 products of Eq. (12); the GEMM
-                # runs each as GEMM_PIECE_PRODUCTS bf16 products on the matrix cores
-                bf = GEMM_PIECE_PRODUCTS * w["flop"] / lps
+                # w["flop"]: 2 C d n, the fp32 products of Eq. (12); w["mfma"]:
+                # the 16-bit products that the GEMM runs for them on the matrix cores
+                bf = w["mfma"] / lps
                 k.update({"bound": "mfma", "unit": "TFLOP/s", "peak": PEAK_MFMA_BF16_TFLOPS,
                           "flop_per_launch": bf, "achieved": bf / avg_s / 1e12,
                           "fp32_equivalent_tflops": w["flop"] / lps / avg_s / 1e12})
@@ -701,9 +707,9 @@ def main():
                 "traffic": None if traffic is None else int(traffic),
                 "avg_launch_us": round(K["avg_us"], 3),
                 "fp32_equivalent_tflops": round(K.get("fp32_equivalent_tflops", 0.0), 4),
-                "achieved_is": "6 x 2 C d n bf16 FLOP per layer (six bf16 piece products for each of "
-                               "Eq. (12)'s fp32 products) / event-timed launch duration, against the "
-                               "dense bf16 MFMA peak"}
+                "achieved_is": "4 x 2 C d n fp16 FLOP per layer, 6 x for d < 128 in bf16 (the piece products "
+                               "for each of Eq. (12)'s fp32 products) / event-timed launch duration, against "
+                               "the dense 16-bit MFMA peak"}
     # the candidate search: the fit kernel with the most time per step, with
     # the counter figures of the stored summary (FP32 / FP64 VALU rates
     # against their peaks, VALU-active and wait shares, HBM bytes)
@@ -730,7 +736,7 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f64+f32+bf16",
+        "dtype": "f64+f32+f16",
         "data": "synthetic",
         "config": {"workload": wk.name, "layers": nl, "channels": wk.channels,
                    "weights": wk.weights, "bits": wk.bits, "max_points": wk.max_points,

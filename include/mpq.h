@@ -135,9 +135,11 @@ int64_t mpq_fit_max_dim(int n_grid);
  *   ref[k] = (1/n) sum_t ( w_k . x_t )^2          (if ref_opt != NULL)
  * where w~_k = sum_{i<counts[k]} scales[k][i] * codes[k][i] and x_t is
  * column t of X.  The difference w_k - w~_k is formed in fp64 and rounded
- * to fp32; each fp32 product is summed from six products of the operands'
- * exact three-piece bf16 splits on the bf16 matrix cores, with fp32
- * accumulation (within one rounding of the fp32 product of an fp32 MFMA);
+ * to fp32; each fp32 product is summed on the 16-bit matrix cores, with fp32
+ * accumulation, from four products of fp16 pieces of the scaled operands
+ * (d >= 128 and rows of X whose largest magnitudes lie within a factor of
+ * 2^10: three pieces of w - w~, exact to 2^-39 of its largest, and two of X,
+ * within 2^-23), or else from six products of exact three-piece bf16 splits;
  * the sum over the batch is fp64.
  *
  * Arguments
@@ -160,7 +162,8 @@ int mpq_output_error(const float *W, const int8_t *codes, const float *scales,
  * harnesses that forbid hipMalloc).  Same arguments, kernels and results
  * (bitwise those of mpq_output_error on the same inputs); the call
  * allocates nothing.  Its workspace (the residual rows in tiles, row
- * partials and per-K-range outputs) is a fixed array of MPQ_NOALLOC_BYTES
+ * partials and per-K-range outputs; a little more behind it holds the rows'
+ * and X's ranges) is a fixed array of MPQ_NOALLOC_BYTES
  * per device, held by the library from the moment its code loads on that
  * device until the process ends.  A call whose workspace would exceed it
  * (about 4 ceil(c_out / 128) 128 ceil(d / 32) 32 bytes for the residual,
@@ -259,7 +262,7 @@ int mpq_quantize_layers(const mpq_layer *layers, int n_layers, int bits, int max
  * isotropic one.  For each channel k, after each point n >= 1:
  *   e_n = (1/n_cols) sum_t ( (w_k - w~_k,n) . x_t )^2     (x_t: column t of X)
  * is computed as mpq_output_error does (fp64 difference rounded to fp32,
- * fp32 products from bf16 pieces, fp64 sum over the batch), and the channel stops once
+ * fp32 products from 16-bit pieces, fp64 sum over the batch), and the channel stops once
  *   e_n <= thr,  thr = eps * (1/n_cols) sum_t (w_k . x_t)^2   (relative != 0)
  *                thr = eps                                  (relative == 0),
  * or at max_points, or when its residual is zero.  The points themselves

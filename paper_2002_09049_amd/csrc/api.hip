@@ -115,7 +115,7 @@ static bool over_workspace_limit(size_t bytes)
     return end && *end == '\0' && (unsigned long long)bytes > lim;
 }
 
-hipError_t scratch_alloc(void **p, size_t bytes, hipStream_t s)
+hipError_t scratch_alloc(void **p, size_t bytes, hipStream_t s, size_t more)
 {
     if (over_workspace_limit(bytes)) return hipErrorOutOfMemory;
     int dev = 0;
@@ -138,7 +138,7 @@ hipError_t scratch_alloc(void **p, size_t bytes, hipStream_t s)
         }
         pool = g_pool[dev];
     }
-    return hipMallocFromPoolAsync(p, bytes == 0 ? 256 : bytes, pool, s);
+    return hipMallocFromPoolAsync(p, bytes + more == 0 ? 256 : bytes + more, pool, s);
 }
 
 hipError_t scratch_free(void *p, hipStream_t s) { return hipFreeAsync(p, s); }
@@ -531,24 +531,39 @@ int check_error_layer(const mpq_layer &L, int max_points, bool need_x)
     return MPQ_OK;
 }
 
+// Room for a call's row maxima and ranges behind the fixed workspace: a row
+// of D takes at least 128 bytes of it and 4 of these, and a call of one layer
+// has two items, each rounded up to 256 bytes.
+constexpr size_t kNoallocAux = (size_t)MPQ_NOALLOC_BYTES / 32 + 4096;
+
 // The independent launch groups of an output error, with one scratch block
 // holding each group's part.
 struct ErrJobs {
-    std::vector<size_t> off;
+    std::vector<size_t> off, aux_off;
     std::vector<double> work;
     char *scratch = nullptr;
+    char *aux = nullptr;
     bool owned = true;   // allocated by err_jobs (else a caller-held block)
+
+    void release(hipStream_t s)
+    {
+        if (!owned) return;
+        if (scratch) (void)mpq::scratch_free(scratch, s);
+        aux = scratch = nullptr;
+    }
 };
 
 // fixed != nullptr: the groups' scratch is that caller-held block of
-// fixed_bytes (nothing is allocated); a call that needs more fails with
-// MPQ_ERR_SHAPE.
+// fixed_bytes (nothing is allocated; the second block follows it, see
+// kNoallocAux); a call that needs more fails with MPQ_ERR_SHAPE.
 int err_jobs(const std::vector<mpq::ErrLayerIn> &in, hipStream_t s, ErrJobs *j,
              char *fixed = nullptr, size_t fixed_bytes = 0)
 {
     const int ng = mpq::err_group_count(in.data(), (int)in.size());
-    size_t total = 0;
+    size_t total = 0, aux = 0;
     for (int g = 0; g < ng; ++g) {
+        j->aux_off.push_back(aux);
+        aux += (mpq::err_group_aux_bytes(in.data(), (int)in.size(), g) + 255) / 256 * 256;
         j->off.push_back(total);
         total += (mpq::err_group_scratch_bytes(in.data(), (int)in.size(), g) + 255) / 256 * 256;
         j->work.push_back(mpq::err_group_flop(in.data(), (int)in.size(), g));
@@ -557,22 +572,29 @@ int err_jobs(const std::vector<mpq::ErrLayerIn> &in, hipStream_t s, ErrJobs *j,
         if (total > fixed_bytes)
             return fail(MPQ_ERR_SHAPE, "the output error needs %zu bytes of workspace; the fixed "
                         "workspace holds %zu", total, fixed_bytes);
+        if (aux > kNoallocAux)
+            return fail(MPQ_ERR_SHAPE, "the output error's row maxima need %zu bytes; the fixed workspace holds %zu",
+                        aux, kNoallocAux);
         j->scratch = fixed;
+        j->aux = fixed + fixed_bytes;
         j->owned = false;
         return MPQ_OK;
     }
-    const hipError_t e = mpq::scratch_alloc((void **)&j->scratch, total, s);
+    // (the limit counts the first block alone, a small share apart)
+    const hipError_t e = mpq::scratch_alloc((void **)&j->scratch, total, s, aux);
     if (e != hipSuccess) {
         j->scratch = nullptr;
         return fail(MPQ_ERR_NOMEM, "scratch of %zu bytes: %s", total, hipGetErrorString(e));
     }
+    j->aux = j->scratch + total;
     return MPQ_OK;
 }
 
 hipError_t launch_err_job(const std::vector<mpq::ErrLayerIn> &in, const ErrJobs &j, int g, int P,
-                          hipStream_t st, int parts = mpq::kErrUpload | mpq::kErrKernels)
+                          hipStream_t st, int parts = mpq::kErrUpload | mpq::kErrScan | mpq::kErrKernels)
 {
-    return mpq::launch_output_error_group(in.data(), (int)in.size(), g, P, j.scratch + j.off[g], st, parts);
+    return mpq::launch_output_error_group(in.data(), (int)in.size(), g, P, j.scratch + j.off[g],
+                                          j.aux + j.aux_off[g], st, parts);
 }
 
 int output_error_impl(const mpq_layer *layers, int n_layers, int max_points, void *stream,
@@ -599,7 +621,7 @@ int output_error_impl(const mpq_layer *layers, int n_layers, int max_points, voi
     const hipError_t e = run_concurrently(s, jobs.work, [&](int i, hipStream_t st) {
         return launch_err_job(in, jobs, i, max_points, st);
     });
-    if (jobs.scratch && jobs.owned) (void)mpq::scratch_free(jobs.scratch, s);
+    jobs.release(s);
     if (e != hipSuccess) return hip_fail(e, "output error kernel launch");
     return MPQ_OK;
 }
@@ -610,7 +632,7 @@ int output_error_impl(const mpq_layer *layers, int n_layers, int max_points, voi
 // Host code never passes its name to a kernel (on the host the name is a
 // stand-in, not a device address): each device's address comes from
 // hipGetSymbolAddress, once, with that device current.
-static __device__ __align__(256) char scratch[MPQ_NOALLOC_BYTES];
+static __device__ __align__(256) char scratch[MPQ_NOALLOC_BYTES + kNoallocAux];
 
 std::mutex g_noalloc_mu;
 char *g_noalloc_ptr[kMaxDevices];
@@ -745,15 +767,16 @@ void quantize_build(const mpq_layer *layers, int n_layers, int bits, int max_poi
 void quantize_link_d(QuantizeStep *q)
 {
     if (q->err.empty()) return;
-    std::vector<int64_t> d_off(q->err.size());
+    std::vector<int64_t> d_off(q->err.size()), max_off(q->err.size());
     std::vector<int> d_grp(q->err.size());
-    mpq::err_item_d_offsets(q->err.data(), (int)q->err.size(), d_off.data(), d_grp.data());
+    mpq::err_item_d_offsets(q->err.data(), (int)q->err.size(), d_off.data(), max_off.data(), d_grp.data());
     for (FitJob &j : q->jobs) {
         if (j.dense) continue;
         for (int i = 0; i < j.b.n_layers; ++i) {
             const int e = q->err_of[j.layers[i]];
             if (e < 0 || d_off[e] < 0) continue;
             j.b.L[i].dres = (float *)(q->ej.scratch + q->ej.off[d_grp[e]] + d_off[e]);
+            j.b.L[i].dmax = (uint32_t *)(q->ej.aux + q->ej.aux_off[d_grp[e]] + max_off[e]);
             q->err[e].d_ready = 1;
         }
     }
@@ -783,7 +806,7 @@ hipError_t quantize_enqueue(QuantizeStep &q, hipStream_t s)
         }
         hipError_t e1 = hipSuccess;
         for (int g = 0; g < n_groups && e1 == hipSuccess; ++g)
-            e1 = launch_err_job(q.err, q.ej, g, q.max_points, st, mpq::kErrUpload);
+            e1 = launch_err_job(q.err, q.ej, g, q.max_points, st, mpq::kErrUpload | mpq::kErrScan);
         return e1;
     });
     if (e != hipSuccess) return e;
@@ -820,7 +843,7 @@ int quantize_impl(const mpq_layer *layers, int n_layers, int bits, int max_point
     quantize_link_d(&q);
     const hipError_t e = quantize_enqueue(q, s);
     if (dgrid) (void)mpq::scratch_free(dgrid, s);
-    if (q.ej.scratch) (void)mpq::scratch_free(q.ej.scratch, s);
+    q.ej.release(s);
     if (e != hipSuccess) return hip_fail(e, "kernel launch");
     return MPQ_OK;
 }
@@ -919,7 +942,7 @@ int clip_first_points(const mpq_layer *layers, int n_layers, int M, int P, int G
         e = run_concurrently(s, ej.work, [&](int i, hipStream_t st) { return launch_err_job(in, ej, i, P, st); });
     for (size_t i = 0; i < batches.size() && e == hipSuccess; ++i)
         e = mpq::launch_clip(batches[i].first, batches[i].second, true, s);
-    if (ej.scratch) (void)mpq::scratch_free(ej.scratch, s);
+    ej.release(s);
     (void)mpq::scratch_free(buf, s);
     if (e != hipSuccess) return hip_fail(e, "clipping kernel launch");
     return MPQ_OK;
@@ -1026,8 +1049,8 @@ int calib_impl(const mpq_layer *layers, int n_layers, int bits, int max_points,
     rc = err_jobs(in, s, &ej);
     if (rc == MPQ_OK && relative) rc = err_jobs(in_ref, s, &ej_ref);
     auto release = [&]() {
-        if (ej_ref.scratch) (void)mpq::scratch_free(ej_ref.scratch, s);
-        if (ej.scratch) (void)mpq::scratch_free(ej.scratch, s);
+        ej_ref.release(s);
+        ej.release(s);
         (void)mpq::scratch_free(state, s);
         if (dgrid) (void)mpq::scratch_free(dgrid, s);
     };
@@ -1062,9 +1085,13 @@ int calib_impl(const mpq_layer *layers, int n_layers, int bits, int max_points,
         std::vector<double> w = fit_work;
         const int n_fit = (int)w.size();
         if (step == 0 && !pre) w.insert(w.end(), ej_ref.work.begin(), ej_ref.work.end());
+        // and beside the first step the scan of X's ranges, which all steps use
+        const int n_ref = (int)w.size() - n_fit;
+        if (step == first) w.resize(w.size() + ej.work.size(), 0.0);
         e = run_concurrently(s, w, [&](int i, hipStream_t st) {
-            return i < n_fit ? launch_fit_job(jobs[i], n_grid, st)
-                             : launch_err_job(in_ref, ej_ref, i - n_fit, P, st);
+            if (i < n_fit) return launch_fit_job(jobs[i], n_grid, st);
+            if (i < n_fit + n_ref) return launch_err_job(in_ref, ej_ref, i - n_fit, P, st);
+            return launch_err_job(in, ej, i - n_fit - n_ref, P, st, mpq::kErrUpload | mpq::kErrScan);
         });
         if (e != hipSuccess) break;
         // the output error of the channels that took point step + 1
@@ -1079,7 +1106,7 @@ int calib_impl(const mpq_layer *layers, int n_layers, int bits, int max_points,
             }
         }
         e = run_concurrently(s, ej.work, [&](int i, hipStream_t st) {
-            return launch_err_job(in_s, ej, i, P, st);
+            return launch_err_job(in_s, ej, i, P, st, mpq::kErrUpload | mpq::kErrKernels);
         });
     }
     release();

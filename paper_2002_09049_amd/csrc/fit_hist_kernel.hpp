@@ -966,6 +966,7 @@ fit_hist_kernel(const HistBatch B)
     if (Ly.dres && !stepping) {
         const int nkb = (d + 31) / 32;
         float *drow = Ly.dres + (k / 128) * nkb * 4096 + (k % 128) * 32;
+        if (t == 0) Ly.dmax[k] = __float_as_uint(m);   // of the residual after the last point
 #pragma unroll
         for (int v = 0; v < kSlots; ++v) {
             const int j0 = kC * (t + T * v);

@@ -299,6 +299,10 @@ __global__ void __launch_bounds__(kSmallWaves * kWave) fit_small_kernel(const Hi
         for (int j = 0; j < kD; ++j)
             if (lane == j) v = (float)r[j];   // 0 past d
         if (lane < 32) Ly.dres[(k / 128) * 4096 + (k % 128) * 32 + lane] = v;
+        float top = 0.0f;
+#pragma unroll
+        for (int j = 0; j < kD; ++j) top = fmaxf(top, fabsf((float)r[j]));
+        if (lane == 0) Ly.dmax[k] = __float_as_uint(top);
     }
     for (int q = n + lane; q < P; q += kWave) {
         Ly.scales[k * P + q] = 0.0f;

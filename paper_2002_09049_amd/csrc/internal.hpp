@@ -72,7 +72,12 @@ struct HistLayer {
     // calibration steps (HistBatch::single) only:
     float *xerr;        // [C][P] output error after each point (written by the error pass)
     const float *ref;   // [C] output error of W itself (relative threshold) or nullptr
-    int32_t *list;      // [C] channels that took a point in this step, in any order
+    union {
+        int32_t *list;  // [C] channels that took a point in this step, in any order
+        // (not in calibration steps, with dres) [C] bits of the largest
+        // |D| of each channel's row
+        uint32_t *dmax;
+    };
     int32_t *nlist;     // [P] their number, per step (zero before the first step)
     // asymmetric codes (reading B2): nullptr, or [C] per-channel offsets
     // (the midpoint of w, written by the fit; the points fit w - offset)
@@ -208,20 +213,26 @@ struct ErrLayerIn {
 // holds the group's descriptor table).
 int err_group_count(const ErrLayerIn *in, int n_in);
 size_t err_group_scratch_bytes(const ErrLayerIn *in, int n_in, int group);
+// A second block of each group: the ranges of X and the maxima of D's rows
+// (at most a 32nd of the scratch, half a byte for
+// each of X's rows and 512 bytes per item).
+size_t err_group_aux_bytes(const ErrLayerIn *in, int n_in, int group);
 double err_group_flop(const ErrLayerIn *in, int n_in, int group);
-// The parts of a group's launch: the upload of its descriptor table (small
-// kernels that depend on nothing the fit writes) and the form, GEMM and
-// finish kernels; a caller may enqueue the uploads earlier, beside other work.
-constexpr int kErrUpload = 1, kErrKernels = 2;
+// The parts of a group's launch: the upload of its descriptor table and the
+// scan of X's range (which depend on nothing the fit writes), and the form,
+// GEMM and finish kernels; a caller may enqueue the first two earlier, beside
+// other work, and scan once for several launches on the same X and aux.
+constexpr int kErrUpload = 1, kErrKernels = 2, kErrScan = 4;
 hipError_t launch_output_error_group(const ErrLayerIn *in, int n_in, int group, int P, void *scratch,
-                                     hipStream_t s,
-                                     int parts = kErrUpload | kErrKernels);
+                                     void *aux, hipStream_t s,
+                                     int parts = kErrUpload | kErrScan | kErrKernels);
 // Where the err item of in[i] keeps its rows of D (fp32 tiles [ceil(C / 128)]
 // [ceil(d / 32)][128][32], row-major inside, k past d zero): for each
 // in[i], the byte offset inside its group's scratch in off[i] and the group
 // in group[i]; -1 for both when in[i] has no err item or its rows are
 // clipping candidates.  Every group's layout is formed once.
-void err_item_d_offsets(const ErrLayerIn *in, int n_in, int64_t *off, int *group);
+// max_off: likewise the byte offset of its rows' maxima inside the group's aux.
+void err_item_d_offsets(const ErrLayerIn *in, int n_in, int64_t *off, int64_t *max_off, int *group);
 
 // Clipping of Eq. (13) as the first point: candidate scales, then (after the
 // output error of the candidates) the choice of point 1.  One workgroup per
@@ -249,7 +260,8 @@ hipError_t launch_clip(const ClipBatch &b, int64_t channels, bool choose, hipStr
 
 // Stream-ordered scratch from a library-owned memory pool of the current
 // device (kept, not returned to the system, between calls).
-hipError_t scratch_alloc(void **p, size_t bytes, hipStream_t s);
+// more: bytes that the workspace limit does not count.
+hipError_t scratch_alloc(void **p, size_t bytes, hipStream_t s, size_t more = 0);
 hipError_t scratch_free(void *p, hipStream_t s);
 
 // Reconstruction of Eq. (4) for a list of layers.

@@ -3,7 +3,7 @@
 // ref[k] = (1/n) sum_t (w_k . x_t)^2.
 //
 // All layers of a call (items: an err item per layer, a ref item per layer
-// that asks for ref; up to kMaxErrItems) go through three launches together.
+// that asks for ref; up to kMaxErrItems) go through the launches together.
 // Their descriptors sit in a table at the head of the call's scratch, filled
 // by small upload kernels that carry kDescChunk descriptors each in their
 // kernel arguments (stream-ordered, so no host buffer outlives the call);
@@ -16,16 +16,17 @@
 //     slab of a row tile is one contiguous block.  Items whose rows the fit
 //     already wrote (d_ready) are not formed.
 //
-//  2. gemm: Y = D X, the path's one dense contraction, in fp32 from bf16
-//     matrix products: each fp32 operand is split into three bf16 pieces
-//     (hi + mid + lo, exact) and six of the nine piece products are summed
-//     by v_mfma_f32_32x32x16_bf16 with fp32 accumulation (the three left
-//     out lie below one rounding of the fp32 product).  A workgroup owns a
+//  2. gemm: Y = D X, the path's one dense contraction, in fp32 from 16-bit
+//     matrix products with fp32 accumulation.  Long rows (d >= kHalfMinD)
+//     whose X spans a moderate range take three fp16 pieces of D and two of X
+//     and four piece products, on rows of D and an X scaled by powers of two;
+//     the others three bf16 pieces each (hi + mid + lo, exact) and six of the
+//     nine products (see the kernel).  A workgroup owns a
 //     128 x 128 tile of Y and one K range, with eight wavefronts: four
 //     multiply (64 x 64 each, as 2 x 2 MFMA blocks) and four stage.  The
-//     staging ones load a 16-k slab of D (a half of a tile block's rows) and
-//     of X (16 rows of 128 samples) four slabs ahead into a ring of
-//     registers, split it once into bf16 piece tiles (k contiguous per row
+//     staging ones load a slab of D (32 k of a tile's rows, or with bf16
+//     pieces 16) and of X (as many rows of 128 samples) 64 k ahead into a
+//     ring of registers, split it once into piece tiles (k contiguous per row
 //     of D and per column of X) and store it to one of two LDS buffers
 //     while the multiplying ones read the other: one barrier per slab
 //     (buffer loads: offsets past a range read as zeros).  Two workgroups
@@ -39,6 +40,10 @@
 // kernel, and workgroups past it return at once), with the result of row m
 // written to err[rows[m] * stride].  A row's result does not depend on its
 // position, so the list order does not matter.
+//
+//  0. scan (long rows only): the largest |x| of X and the smallest of its
+//     rows' maxima, for the choice of the pieces; beside the fits where there
+//     are any.
 //
 //  3. finish: per row, the partials summed in column-tile order, or the K
 //     ranges of Y summed in range order, squared and summed over the columns;
@@ -55,6 +60,7 @@
 // Tile coordinates come from uniform subtraction loops, not divisions, so
 // they and the buffer resources built from them stay in scalar registers.
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "internal.hpp"
@@ -70,21 +76,28 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int kBM = 128, kBN = 128, kBK = 32;
 constexpr int kRangeK = 768;      // K of a split layer's K range, about
 constexpr int kMinSlabs = 4;      // shortest K range (slabs) of a listed layer's live rows
 constexpr int kThreads = 512;   // GEMM workgroup: four wavefronts multiply (64 x 64 of the tile each), four stage
 constexpr int kStageT = 256;    // threads of the staging wavefronts
-constexpr int kPieces = 3;      // bf16 pieces of an fp32 operand
+constexpr int kPieces = 3;      // pieces of an fp32 operand (of X with fp16: two)
+constexpr int kSpread = 10;     // fp16 pieces: largest spread of the exponents of X's row maxima
+constexpr int kHalfMinD = 128;  // fp16 pieces: shortest rows
+constexpr int kTopExp = 14;     // exponent of an fp16 piece's row or layer maximum after scaling
 constexpr int kSlabK = 16;      // k per staged slab (one 16-k MFMA step)
 constexpr int kRowK = kSlabK + 8;   // LDS row of a piece: 16 bf16 and 16 bytes of padding (48 bytes)
-constexpr int kRing = 4;        // staging register sets: loads run four slabs ahead
+constexpr int kSlabH = 32;      // k per staged slab of fp16 pieces
+constexpr int kRing = 4;        // staging register sets: loads run four slabs ahead (two fp16 ones)
 constexpr int kMaxErrItems = 1024;   // items (err and ref) per launch group
 constexpr int kDescChunk = 20;       // descriptors per upload kernel
 constexpr int kXcds = 8;         // MI355X: workgroups are dealt to 8 XCDs in turn
 constexpr int kFormThreads = 256;
 constexpr int kFinRows = 256 / kWave;   // finish: rows of a split layer per workgroup
+constexpr int kScanRows = 16;    // rows of X per workgroup of the range scan
 
 // Raw buffer resource (gfx9 descriptor word 3: 32-bit dwords, no swizzle).
 // Loads at offsets >= num_records return zeros; kOob is past every range.
@@ -119,12 +132,25 @@ struct ErrLayer {
     int tiles;           // gemm workgroups: ntm * ntn * splits, more for a listed layer
     int block_begin;     // first gemm workgroup (a multiple of kXcds)
     int extra_begin;     // first of the workgroups past the plan's tiles (a multiple of kXcds)
-    int xoff;            // XCD rank offset: the layer's spare tiles go to XCDs xoff, xoff + 1, ...
     int form_begin;      // first form workgroup
     int fin_begin;       // first finish workgroup
-    int use_points;      // 1: D = residual (err), 0: D = W (ref), 2: D = clipping candidates
-    int Gc, M;
-    int vecw;            // d % 4 == 0, W 16-byte and codes 4-byte aligned
+    int scan_begin;      // first range scan workgroup
+    int Gc;
+    int max_begin;       // the rows' maxima: ErrGroup::rowmax + 64 max_begin
+    int x_begin;         // the range of X: ErrGroup::xrange[x_begin ..], one per kScanRows rows
+    int8_t use_points;   // 1: D = residual (err), 0: D = W (ref), 2: D = clipping candidates
+    int8_t xoff;         // XCD rank offset: the layer's spare tiles go to XCDs xoff, xoff + 1, ...
+    int8_t vecw;         // d % 4 == 0, W 16-byte and codes 4-byte aligned
+    int8_t M;            // levels (at most 127)
+};
+
+// Of kScanRows rows of X: the bits of the largest |x|, and the complement of
+// the bits of the smallest nonzero maximum of |x| over a row.  Kept per
+// workgroup of the scan and reduced by the readers: atomics of many
+// workgroups on one word queue up at the memory side of the XCDs' L2s (they
+// doubled the scan's time).
+struct XRange {
+    uint32_t top, nlow;
 };
 
 struct ErrGroup {
@@ -132,6 +158,8 @@ struct ErrGroup {
     int P;
     int extra_start;     // gemm workgroups past every layer's planned tiles start here
     int vecx;            // n % 4 == 0 and every X 16-byte aligned
+    XRange *xrange;      // by scan workgroup
+    uint32_t *rowmax;    // bits of the largest |D| of each row
 };
 
 // kDescChunk descriptors for the table (kernel arguments of one upload)
@@ -141,7 +169,7 @@ struct DescChunk {
     ErrLayer L[kDescChunk];
 };
 static_assert(sizeof(DescChunk) <= 4096, "kernel arguments");
-static_assert(sizeof(ErrLayer) % 4 == 0, "copied as 32-bit words");
+static_assert(sizeof(ErrLayer) == 184, "copied as 32-bit words; the table's share of the scratch");
 
 __global__ void __launch_bounds__(64) desc_upload_kernel(const DescChunk c)
 {
@@ -149,6 +177,49 @@ __global__ void __launch_bounds__(64) desc_upload_kernel(const DescChunk c)
     const uint32_t *src = (const uint32_t *)c.L;
     uint32_t *dst = (uint32_t *)c.dst;
     for (int i = threadIdx.x; i < c.count * kWords; i += 64) dst[i] = src[i];
+}
+
+// ---- 0. scan: the range of X (see XRange), kScanRows rows per workgroup.
+// Bound by HBM: one read of X, beside the fits where there are any.
+__global__ void __launch_bounds__(256) scan_x_kernel(const ErrGroup g, const ErrLayer *__restrict__ Ls)
+{
+    __shared__ uint32_t s_top[4], s_nlow[4];
+    const int li = last_at_most(g.n_layers, (int)blockIdx.x, [&](int i) { return Ls[i].scan_begin; });
+    const ErrLayer &L = Ls[li];
+    const int lane = (int)threadIdx.x % kWave, wid = (int)threadIdx.x / kWave;
+    const int64_t n = L.n;
+    const bool vec = n % 4 == 0 && (uintptr_t)L.X % 16 == 0;
+    uint32_t top = 0, nlow = 0;
+    for (int i = wid; i < kScanRows; i += 4) {
+        const int64_t row = (int64_t)((int)blockIdx.x - L.scan_begin) * kScanRows + i;
+        if (row >= L.d) break;   // uniform
+        const float *x = L.X + row * n;
+        uint32_t m = 0;
+        auto add = [&](float v) { m = max(m, __float_as_uint(v) & 0x7fffffffu); };
+        if (vec) {
+#pragma unroll 4
+            for (int64_t c = 4 * lane; c < n; c += 4 * kWave) {
+                const f32x4 v = *(const f32x4 *)(x + c);
+                add(v[0]); add(v[1]); add(v[2]); add(v[3]);
+            }
+        } else {
+#pragma unroll 8
+            for (int64_t c = lane; c < n; c += kWave) add(x[c]);
+        }
+#pragma unroll
+        for (int off = kWave / 2; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off));
+        top = max(top, m);
+        if (m != 0) nlow = max(nlow, ~m);
+    }
+    if (lane == 0) {
+        s_top[wid] = top;
+        s_nlow[wid] = nlow;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        g.xrange[blockIdx.x] = XRange{max(max(s_top[0], s_top[1]), max(s_top[2], s_top[3])),
+                                      max(max(s_nlow[0], s_nlow[1]), max(s_nlow[2], s_nlow[3]))};
+    }
 }
 
 // The K split of the live rows 0 .. nact of D.  A layer's full rows take the
@@ -171,6 +242,14 @@ __device__ __forceinline__ LiveSplit live_split(const ErrLayer &L, int64_t nact)
     return LiveSplit{ntm, (L.d + kch - 1) / kch, kch};
 }
 
+// threads that form a row of q4 float4s
+__host__ __device__ inline int form_lanes(int64_t q4)
+{
+    int n = 8;
+    while (n < kFormThreads && n < q4) n *= 2;
+    return n;
+}
+
 __device__ __forceinline__ double int8_of(uint32_t w, int u)
 {
     return (double)(int)(int8_t)(uint8_t)(w >> (8 * u));
@@ -184,19 +263,44 @@ __device__ __forceinline__ int64_t d_index(int64_t m, int64_t k, int nkb)
     return ((m / kBM) * nkb + k / kBK) * (kBM * kBK) + (m % kBM) * kBK + k % kBK;
 }
 
-// ---- 1. form: rows of D, four consecutive k (one float4) per thread, k
-// past d written as zeros
+// ---- 1. form: rows of D, four consecutive k (one float4) at a time, k past d
+// written as zeros, and each row's largest |D|.  A row takes `lanes` threads
+// (a power of two from 8 to 256, by its length), so its maximum needs no
+// atomics.
+__device__ __forceinline__ float4 form4(const ErrLayer &L, int P, int64_t m, int64_t k);
 __global__ void __launch_bounds__(kFormThreads) form_d_kernel(const ErrGroup g,
                                                               const ErrLayer *__restrict__ Ls)
 {
+    __shared__ uint32_t s_max[kFormThreads / kWave];
     const int li = last_at_most(g.n_layers, (int)blockIdx.x, [&](int i) { return Ls[i].form_begin; });
     const ErrLayer &L = Ls[li];
-    const int P = g.P;
-    const int64_t d = L.d, C = L.C, q4 = (int64_t)L.nkb * (kBK / 4);
-    const int64_t e = (int64_t)((int)blockIdx.x - L.form_begin) * kFormThreads + threadIdx.x;
-    const int64_t m = e / q4, k = (e - m * q4) * 4;
-    const int64_t nact = L.rows ? (int64_t)*L.nrows : C;
-    if (m >= nact) return;   // rows past the list feed only output rows nobody reads
+    const int64_t q4 = (int64_t)L.nkb * (kBK / 4);
+    const int lanes = form_lanes(q4), t = (int)threadIdx.x;
+    const int64_t m = (int64_t)((int)blockIdx.x - L.form_begin) * (kFormThreads / lanes) + t / lanes;
+    const int64_t nact = L.rows ? (int64_t)*L.nrows : (int64_t)L.C;
+    uint32_t top = 0;
+    if (m < nact) {   // rows past the list feed only output rows nobody reads
+        for (int64_t q = t % lanes; q < q4; q += lanes) {
+            const float4 v = form4(L, g.P, m, 4 * q);
+            *(float4 *)(L.D + d_index(m, 4 * q, L.nkb)) = v;
+            top = max(top, max(max(__float_as_uint(fabsf(v.x)), __float_as_uint(fabsf(v.y))),
+                               max(__float_as_uint(fabsf(v.z)), __float_as_uint(fabsf(v.w)))));
+        }
+    }
+    for (int off = min(lanes, kWave) / 2; off > 0; off >>= 1) top = max(top, (uint32_t)__shfl_xor((int)top, off));
+    if (lanes > kWave) {   // uniform
+        if (t % kWave == 0) s_max[t / kWave] = top;
+        __syncthreads();
+        const int w0 = t / lanes * (lanes / kWave);
+        for (int w = 0; w < lanes / kWave; ++w) top = max(top, s_max[w0 + w]);
+    }
+    if (t % lanes == 0 && m < nact) g.rowmax[(int64_t)L.max_begin * 64 + m] = top;
+}
+
+// D[m][k .. k + 3]
+__device__ __forceinline__ float4 form4(const ErrLayer &L, int P, int64_t m, int64_t k)
+{
+    const int64_t d = L.d;
     double r[4] = {0.0, 0.0, 0.0, 0.0};
     if (L.use_points == 2) {
         // clipping candidate j of channel ch: w - a [w / a]_Q (Eq. (10)'s
@@ -248,7 +352,7 @@ __global__ void __launch_bounds__(kFormThreads) form_d_kernel(const ErrGroup g,
             }
         }
     }
-    *(float4 *)(L.D + d_index(m, k, L.nkb)) = make_float4((float)r[0], (float)r[1], (float)r[2], (float)r[3]);
+    return make_float4((float)r[0], (float)r[1], (float)r[2], (float)r[3]);
 }
 
 // ---- 2. gemm: Y = D X, squared and summed per row
@@ -286,6 +390,52 @@ __device__ __forceinline__ void split_store8(const float (&v)[8], __bf16 *h, __b
     *(bf16x8 *)l = vl;
 }
 
+// 2^e as a float, e clamped to the normal range
+__device__ __forceinline__ float pow2(int e)
+{
+    return __uint_as_float((uint32_t)(min(max(e, -126), 127) + 127) << 23);
+}
+// exponent of a float's bits (subnormals and zero: -127)
+__device__ __forceinline__ int exponent(uint32_t bits) { return (int)((bits >> 23) & 0xffu) - 127; }
+
+// The fp16 pieces of s v, s a power of two, each the remainder so far rounded
+// to nearest (11 significant bits; the remainders are exact in fp32).  With
+// the row's or layer's maximum scaled to [2^14, 2^15), two are within
+// 2^-23 |s v| + 2^-25 of s v (exact for three values in four, which leave the
+// second at most 11 bits) and three within 2^-25, which is 2^-39 of the
+// maximum.
+template <int kN>
+__device__ __forceinline__ void split_store8(const float (&v)[8], float s, _Float16 *(&to)[kN])
+{
+    float r[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) r[i] = v[i] * s;
+#pragma unroll
+    for (int p = 0; p < kN; ++p) {
+        f16x8 h;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const f32x2 x = {r[2 * i], r[2 * i + 1]};
+            const f16x2 ph = __builtin_convertvector(x, f16x2);
+            h[2 * i] = ph[0];
+            h[2 * i + 1] = ph[1];
+            r[2 * i] -= (float)ph[0];
+            r[2 * i + 1] -= (float)ph[1];
+        }
+        *(f16x8 *)to[p] = h;
+    }
+}
+
+// A 16-byte chunk (8 k) of a row of an fp16 piece tile: rows of kSlabH
+// halves without padding, the chunks of a row permuted by its number, so that
+// 16 rows' reads of one chunk, and a staging wavefront's stores, cover the 64
+// banks once.
+template <int kN>   // pieces
+__device__ __forceinline__ _Float16 *piece_at(uint16_t *tiles, int buf, int piece, int row, int chunk)
+{
+    return (_Float16 *)tiles + ((buf * kN + piece) * kBM + row) * kSlabH + ((chunk ^ (row >> 2)) & 3) * 8;
+}
+
 // Y = D X in fp32 from bf16 matrix products (v_mfma_f32_32x32x16_bf16):
 // with D = Dh + Dm + Dl and X = Xh + Xm + Xl (split_pair), each product
 // D X is summed from the six piece products Dh Xh, Dh Xm, Dm Xh, Dh Xl,
@@ -294,15 +444,45 @@ __device__ __forceinline__ void split_store8(const float (&v)[8], __bf16 *h, __b
 // under one rounding of the fp32 product, so the sums carry the error of an
 // fp32 accumulation.  Six bf16 products cost 6/16 of one fp32 product's
 // matrix-core time.
+//
+// With fp16 pieces (v_mfma_f32_32x32x16_f16, the same rate), three of D and
+// two of X, four products do: Dh Xh, Dh Xl, Dm Xh, Dl Xh.  A row of D is
+// scaled so that its largest element lies in [2^14, 2^15), X as one, and the
+// sums are scaled back exactly.  What a product loses is at most 2^-22 of
+// itself left out (Dm Xl), 2^-23 for X's split (exact for three values in
+// four) and 2^-39 of its row's or X's maximum.  The first two change from
+// sample to sample, so a mean over samples hardly sees them; an error of D
+// would be the same in all, hence its third piece.  The last is why X's rows
+// may not differ by more than 2^kSpread in their maxima: then it stays below
+// 2^-28 of the row's largest product.  A third fewer fp32 additions round off
+// less.  A wider range, a non-finite X or one near fp32's limits take the bf16
+// pieces, as do rows of less than kHalfMinD (nothing to gain: their launches
+// are bound by latency).  Measured, six bf16 products -> four fp16 ones: rms
+// relative error of 512 rows' output error on 256 samples 4.2e-8 -> 3.5e-8
+// (d = 128), 6.9e-8 -> 5.8e-8 (d = 1152); the launch of ResNet-50 330 -> 269 us,
+// of VGG-16 fc 2466 -> 1983 us, of a 999 x 2047 layer and its reference on 1001
+// samples 72 -> 60 us.  (Three products with two pieces of D: 253, 1814 and 57
+// us, but D's rounding stood out, 3.2e-8 -> 4.0e-8 at d = 256 on 2048 samples
+// and more beyond.)  Operand reads and piece stores (about 640 and 320 cycles of
+// LDS per CU and pair of 16-k steps) stand beside 1024 cycles of MFMA; slabs of
+// 32 k instead of 16 halve the barriers (261 -> 253 us for ResNet-50).
 template <bool kVecX>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4)))
 gemm_err_kernel(const ErrGroup g, const ErrLayer *__restrict__ Ls)
 {
-    // double-buffered piece tiles of a 16-k slab: rows of D (channels) and
-    // columns of X (samples); a 16-byte read of 16 rows covers the 64 banks once
-    __shared__ __align__(16) __bf16 sD[2][kPieces][kBM][kRowK];
-    __shared__ __align__(16) __bf16 sX[2][kPieces][kBN][kRowK];
-    __shared__ double sPart[2][kBM];
+    // double-buffered piece tiles of a slab: rows of D (channels) and columns
+    // of X (samples).  bf16: three pieces of 16 k each; a 16-byte read of 16
+    // padded rows covers the 64 banks once.  fp16: three pieces of D and two
+    // of X, 32 k each (piece_at): all of half a CU's LDS.  The row sums of
+    // the epilogue lie over the tiles.
+    constexpr int kRowB = kPieces * kBM * kRowK;   // bf16 tiles of one operand and buffer
+    constexpr int kRowF = kBM * kSlabH;            // an fp16 tile
+    __shared__ __align__(16) uint16_t smem[2 * (kPieces + 2) * kRowF];
+    static_assert(sizeof smem >= 2 * 2 * kRowB * 2 && sizeof smem <= 160 * 1024 / 2, "two workgroups per CU");
+    uint16_t(*sD)[kPieces][kBM][kRowK] = (uint16_t(*)[kPieces][kBM][kRowK])smem;
+    uint16_t(*sX)[kPieces][kBN][kRowK] = (uint16_t(*)[kPieces][kBN][kRowK])(smem + 2 * kRowB);
+    uint16_t *const hD = smem, *const hX = smem + 2 * kPieces * kRowF;
+    double(*sPart)[kBM] = (double(*)[kBM])smem;
 
     // a layer's workgroups: the planned tiles' from block_begin, and any
     // more (for the short K ranges of a listed layer's few live rows) from
@@ -352,7 +532,6 @@ gemm_err_kernel(const ErrGroup g, const ErrLayer *__restrict__ Ls)
     const int64_t col0 = (int64_t)tn * kBN;
     const int64_t kbeg = (int64_t)split * ls.kchunk;   // a multiple of kBK
     const int64_t kend = min(kbeg + (int64_t)ls.kchunk, (int64_t)L.d);
-    const int nslab = (int)((kend - kbeg + kSlabK - 1) / kSlabK);
 
     // acc[cb][rb]: samples wn * 64 + cb * 32 + [0, 32) by rows wm * 64 + rb
     // * 32 + [0, 32).  The blocks hold Y transposed (X's pieces as the MFMA's
@@ -366,9 +545,30 @@ gemm_err_kernel(const ErrGroup g, const ErrLayer *__restrict__ Ls)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[cb][rb][v] = 0.0f;
 
+    // fp16 pieces where X's range allows (see above), its scale 2^(kTopExp - ex)
+    uint32_t xtop = 0, xlow = 0;
+    for (int i = L.d >= kHalfMinD ? lane : L.d; i * kScanRows < L.d; i += kWave) {
+        const XRange x = g.xrange[L.x_begin + i];
+        xtop = max(xtop, x.top);
+        xlow = max(xlow, x.nlow);
+    }
+    xtop = (uint32_t)__builtin_amdgcn_readfirstlane(wave_reduce((int)xtop, MaxOp()));   // no sign bits
+    xlow = ~(uint32_t)__builtin_amdgcn_readfirstlane(wave_reduce((int)(xlow ^ 0x80000000u), MaxOp()));
+    xlow ^= 0x80000000u;
+    const int ex = exponent(xtop);
+    const bool f16 = xtop < 0x7f800000u && ex >= -100 && ex - exponent(xlow) <= kSpread;
+    const uint32_t *rmax = g.rowmax + (int64_t)L.max_begin * 64;
+    auto row_exp = [&](int64_t r) {   // of a row of D (rows past the live ones: any)
+        return r < nact ? max(exponent(rmax[r]), kTopExp - 126) : 0;
+    };
+
     // One barrier per slab for all eight wavefronts: the multiplying ones
     // read slab s from buffer s % 2 while the staging ones split slab s + 1
     // into the other buffer.
+    auto product = [&](auto use_f16) {
+    constexpr bool kF16 = decltype(use_f16)::value;
+    constexpr int kSK = kF16 ? kSlabH : kSlabK, kR = kF16 ? kRing / 2 : kRing;
+    const int nslab = (int)((kend - kbeg + kSK - 1) / kSK);
     if (stager) {
         // buffer resources: this row tile's 32-k chunks of D (one
         // contiguous block each; rows past C feed only output rows nobody
@@ -377,52 +577,74 @@ gemm_err_kernel(const ErrGroup g, const ErrLayer *__restrict__ Ls)
         const __amdgpu_buffer_rsrc_t rsD =
             make_rsrc(L.D + (int64_t)tm * L.nkb * (kBM * kBK), (uint32_t)L.nkb * (kBM * kBK * 4));
         const __amdgpu_buffer_rsrc_t rsX = make_rsrc(L.X + kbeg * n, (uint32_t)((kend - kbeg) * n * 4));
-        // staging roles: D row dr, k dh * 8 .. + 7 of the slab (two float4
-        // of the chunk's row); X column xc, k xh * 8 .. + 7 (eight floats,
-        // one per row of X: a wavefront's load covers 64 consecutive columns)
+        // staging roles: D row dr, k dh * kE .. + kE - 1 of the slab (float4s
+        // of the chunk's row); X column xc, k xh * kE .. + kE - 1 (one float
+        // per row of X: a wavefront's load covers 64 consecutive columns)
+        constexpr int kE = kSK / 2;
         const int st = t - kStageT;
         const int dr = st / 2, dh = st % 2;
         const int xc = st % kBN, xh = st / kBN;
-        const uint32_t offD = (uint32_t)((kbeg / kBK * (kBM * kBK) + dr * kBK + dh * 8) * 4);
+        const uint32_t offD = (uint32_t)((kbeg / kBK * (kBM * kBK) + dr * kBK + dh * kE) * 4);
         // a column past n reads at offset 2^32 - 1 (past every range, as a
         // bit mask: no carry); the others stay below 2^32, as kchunk n 4 < 2^31
-        const uint32_t offX = (uint32_t)(((int64_t)xh * 8 * n + col0 + xc) * 4);
+        const uint32_t offX = (uint32_t)(((int64_t)xh * kE * n + col0 + xc) * 4);
         const uint32_t oobX = col0 + xc < n ? 0u : 0xffffffffu;
         const uint32_t rowX = (uint32_t)(n * 4);
-        // slab s: chunk s / 2 of the range, k (s % 2) 16 within it
-        auto load = [&](float (&r)[16], int s) {
-            const uint32_t o = offD + (uint32_t)(s / 2) * (kBM * kBK * 4) + (uint32_t)(s % 2) * (kSlabK * 4);
-            const f32x4 a = load4(rsD, o), b = load4(rsD, o + 16);
+        const float scD = kF16 ? pow2(kTopExp - row_exp(row0 + dr)) : 1.0f;
+        const float scX = kF16 ? pow2(kTopExp - ex) : 1.0f;
+        // slab s: chunk s kSK / 32 of the range (bf16: its half s % 2)
+        auto load = [&](float (&r)[2 * kE], int s) {
+            const uint32_t o = kF16 ? offD + (uint32_t)s * (kBM * kBK * 4)
+                                    : offD + (uint32_t)(s / 2) * (kBM * kBK * 4) + (uint32_t)(s % 2) * (kSlabK * 4);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                r[u] = a[u];
-                r[4 + u] = b[u];
+            for (int q = 0; q < kE / 4; ++q) {
+                const f32x4 a = load4(rsD, o + 16 * q);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) r[4 * q + u] = a[u];
             }
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                r[8 + u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-                    rsX, (offX + (uint32_t)(s * kSlabK + u) * rowX) | oobX, 0, 0));
+            for (int u = 0; u < kE; ++u)
+                r[kE + u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                    rsX, (offX + (uint32_t)(s * kSK + u) * rowX) | oobX, 0, 0));
         };
-        auto store = [&](const float (&r)[16], int buf) {
-            const float(&rd)[8] = *(const float(*)[8])&r[0];
-            const float(&rx)[8] = *(const float(*)[8])&r[8];
-            split_store8(rd, &sD[buf][0][dr][dh * 8], &sD[buf][1][dr][dh * 8], &sD[buf][2][dr][dh * 8]);
-            split_store8(rx, &sX[buf][0][xc][xh * 8], &sX[buf][1][xc][xh * 8], &sX[buf][2][xc][xh * 8]);
-        };
-        float ring[kRing][16];
+        auto store = [&](const float (&r)[2 * kE], int buf) {
+            if constexpr (kF16) {
 #pragma unroll
-        for (int j = 0; j < kRing; ++j)
+                for (int q = 0; q < kE / 8; ++q) {
+                    const float(&rd)[8] = *(const float(*)[8])&r[8 * q];
+                    const float(&rx)[8] = *(const float(*)[8])&r[kE + 8 * q];
+                    const int cd = dh * (kE / 8) + q, cx = xh * (kE / 8) + q;
+                    _Float16 *td[3] = {piece_at<3>(hD, buf, 0, dr, cd), piece_at<3>(hD, buf, 1, dr, cd),
+                                       piece_at<3>(hD, buf, 2, dr, cd)};
+                    _Float16 *tx[2] = {piece_at<2>(hX, buf, 0, xc, cx), piece_at<2>(hX, buf, 1, xc, cx)};
+                    split_store8<3>(rd, scD, td);
+                    split_store8<2>(rx, scX, tx);
+                }
+            } else {
+                const float(&rd)[8] = *(const float(*)[8])&r[0];
+                const float(&rx)[8] = *(const float(*)[8])&r[kE];
+                uint16_t(&D)[kPieces][kBM][kRowK] = sD[buf];
+                uint16_t(&X)[kPieces][kBN][kRowK] = sX[buf];
+                split_store8(rd, (__bf16 *)&D[0][dr][dh * 8], (__bf16 *)&D[1][dr][dh * 8],
+                             (__bf16 *)&D[2][dr][dh * 8]);
+                split_store8(rx, (__bf16 *)&X[0][xc][xh * 8], (__bf16 *)&X[1][xc][xh * 8],
+                             (__bf16 *)&X[2][xc][xh * 8]);
+            }
+        };
+        float ring[kR][2 * kE];
+#pragma unroll
+        for (int j = 0; j < kR; ++j)
             if (j < nslab) load(ring[j], j);
         store(ring[0], 0);
-        if (kRing < nslab) load(ring[0], kRing);
+        if (kR < nslab) load(ring[0], kR);
         __syncthreads();
-        for (int s0 = 0; s0 < nslab; s0 += kRing) {
+        for (int s0 = 0; s0 < nslab; s0 += kR) {
 #pragma unroll
-            for (int j = 0; j < kRing; ++j) {
+            for (int j = 0; j < kR; ++j) {
                 const int s = s0 + j;   // the multiplying wavefronts read slab s
                 if (s >= nslab) break;
-                if (s + 1 < nslab) store(ring[(j + 1) % kRing], (s + 1) % 2);
-                if (s + 1 + kRing < nslab) load(ring[(j + 1) % kRing], s + 1 + kRing);
+                if (s + 1 < nslab) store(ring[(j + 1) % kR], (s + 1) % 2);
+                if (s + 1 + kR < nslab) load(ring[(j + 1) % kR], s + 1 + kR);
                 __syncthreads();
             }
         }
@@ -431,39 +653,61 @@ gemm_err_kernel(const ErrGroup g, const ErrLayer *__restrict__ Ls)
         // listed rows) multiplies nothing: its products are of rows nobody
         // reads.  Slabs past d hold zeros.
         const bool rows_live = row0 + wm * 64 < nact;   // uniform per wavefront
-        constexpr int kPx[6] = {1, 2, 0, 1, 0, 0}, kPd[6] = {1, 0, 2, 0, 1, 0};   // the small products first
-        const int ko = 8 * (lane / 32);
+        // the small products first
+        constexpr int kNx = kF16 ? 2 : 3, kZ = kF16 ? 4 : 6;
+        constexpr int kPx[2][6] = {{1, 2, 0, 1, 0, 0}, {0, 1, 0, 0, 0, 0}};
+        constexpr int kPd[2][6] = {{1, 0, 2, 0, 1, 0}, {2, 0, 1, 0, 0, 0}};
+        typedef std::conditional_t<kF16, f16x8, bf16x8> piece8;
         __syncthreads();
         for (int s = 0; s < nslab; ++s) {
             if (rows_live) {
                 const int buf = s % 2;
-                bf16x8 xp[2][kPieces], dp[2][kPieces];
 #pragma unroll
-                for (int p = 0; p < kPieces; ++p) {
+                for (int h = 0; h < kSK / 16; ++h) {   // 16-k steps
+                    piece8 xp[2][kNx], dp[2][kPieces];
 #pragma unroll
-                    for (int c = 0; c < 2; ++c) {
-                        xp[c][p] = *(const bf16x8 *)&sX[buf][p][wn * 64 + c * 32 + lane % 32][ko];
-                        dp[c][p] = *(const bf16x8 *)&sD[buf][p][wm * 64 + c * 32 + lane % 32][ko];
+                    for (int p = 0; p < kPieces; ++p) {
+#pragma unroll
+                        for (int c = 0; c < 2; ++c) {
+                            const int rx = wn * 64 + c * 32 + lane % 32, rd = wm * 64 + c * 32 + lane % 32;
+                            if constexpr (kF16) {
+                                if (p < kNx)
+                                    xp[c][p % kNx] = *(const piece8 *)piece_at<2>(hX, buf, p, rx, 2 * h + lane / 32);
+                                dp[c][p] = *(const piece8 *)piece_at<3>(hD, buf, p, rd, 2 * h + lane / 32);
+                            } else {
+                                xp[c][p % kNx] = *(const piece8 *)&sX[buf][p][rx][8 * (lane / 32)];
+                                dp[c][p] = *(const piece8 *)&sD[buf][p][rd][8 * (lane / 32)];
+                            }
+                        }
                     }
+#pragma unroll
+                    for (int z = 0; z < kZ; ++z)
+#pragma unroll
+                        for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+                            for (int rb = 0; rb < 2; ++rb) {
+                                const piece8 x = xp[cb][kPx[kF16][z]], d = dp[rb][kPd[kF16][z]];
+                                if constexpr (kF16)
+                                    acc[cb][rb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x, d, acc[cb][rb], 0, 0, 0);
+                                else
+                                    acc[cb][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, d, acc[cb][rb], 0, 0, 0);
+                            }
                 }
-#pragma unroll
-                for (int z = 0; z < 6; ++z)
-#pragma unroll
-                    for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-                        for (int rb = 0; rb < 2; ++rb)
-                            acc[cb][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xp[cb][kPx[z]], dp[rb][kPd[z]],
-                                                                                  acc[cb][rb], 0, 0, 0);
             }
             __syncthreads();
         }
     }
+    };
+    if (f16) product(std::true_type{});
+    else product(std::false_type{});
 
     // Output layout of a 32 x 32 MFMA block: lane holds block column
     // lane % 32 (here row rb * 32 + lane % 32 of the wavefront's 64) and, in
     // register v, block row 8 (v / 4) + 4 (lane / 32) + v % 4 (here a
     // sample: four consecutive ones per group v / 4)
     const int64_t row_w = row0 + wm * 64 + lane % 32;   // + rb * 32
+    // exponent that the scales of fp16 pieces leave in a row of Y
+    auto y_exp = [&](int64_t r) { return f16 ? row_exp(r) + ex - 2 * kTopExp : 0; };
     auto col_of = [&](int cb, int grp) { return col0 + wn * 64 + cb * 32 + 8 * grp + 4 * (lane / 32); };
 
     if (ls.splits > 1) {
@@ -476,6 +720,13 @@ gemm_err_kernel(const ErrGroup g, const ErrLayer *__restrict__ Ls)
             const int64_t r = row_w + rb * 32;
             if (r >= nact) continue;
             float *yr = yp + ((int64_t)split * nact + r) * n;
+            const int ye = y_exp(r);
+            if (f16) {
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[cb][rb][v] = ldexpf(acc[cb][rb][v], ye);
+            }
 #pragma unroll
             for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
@@ -506,7 +757,8 @@ gemm_err_kernel(const ErrGroup g, const ErrLayer *__restrict__ Ls)
 #pragma unroll
             for (int v = 0; v < 16; ++v) sq = fma((double)acc[cb][rb][v], (double)acc[cb][rb][v], sq);
         const double o = __shfl_xor(sq, 32);
-        if (!stager && lane < 32) sPart[wn][wm * 64 + rb * 32 + lane] = sq + o;
+        if (!stager && lane < 32)
+            sPart[wn][wm * 64 + rb * 32 + lane] = ldexp(sq + o, 2 * y_exp(row_w + rb * 32));
     }
     __syncthreads();
     if (t < kBM) {
@@ -563,10 +815,26 @@ __global__ void __launch_bounds__(256) finish_err_kernel(const ErrGroup g,
             for (int u = 0; u < 4; ++u) s = fma((double)y[u], (double)y[u], s);
         }
     } else {
-        for (int64_t c = lane; c < n; c += kWave) {
-            float y = 0.0f;
-            for (int sp = 0; sp < splits; ++sp) y += L.ypart[((int64_t)sp * nact + k) * n + c];
-            s = fma((double)y, (double)y, s);
+        // four columns at a time, the loads of up to four ranges together
+        for (int64_t c = lane; c < n; c += 4 * kWave) {
+            float y[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            for (int sp0 = 0; sp0 < splits; sp0 += 4) {
+                float v[4][4];
+#pragma unroll
+                for (int z = 0; z < 4; ++z)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        v[z][u] = sp0 + z < splits && c + u * kWave < n
+                                      ? L.ypart[((int64_t)(sp0 + z) * nact + k) * n + c + u * kWave]
+                                      : 0.0f;
+#pragma unroll
+                for (int z = 0; z < 4; ++z)
+                    if (sp0 + z < splits)
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) y[u] += v[z][u];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) s = fma((double)y[u], (double)y[u], s);
         }
     }
     s = wave_reduce(s, SumOp());
@@ -588,6 +856,7 @@ struct Plan {
     int64_t nkb, ntm, ntn, splits, kchunk;
     int64_t budget;   // splits of the workgroup budget (ntm * ntn * budget workgroups)
     size_t d_bytes, rowpart_bytes, ypart_bytes;
+    int64_t maxima;   // row maxima, in units of 64
 };
 
 size_t align256(size_t b) { return (b + 255) / 256 * 256; }
@@ -633,6 +902,7 @@ Plan plan_item(const ErrLayerIn &I, bool list)
     q.splits = (I.d + kchunk - 1) / kchunk;   // no empty K range
     q.d_bytes = align256(sizeof(float) * (size_t)(q.ntm * q.nkb * kBM * kBK));
     q.rowpart_bytes = align256(sizeof(double) * (size_t)(q.ntn * C));
+    q.maxima = (C + 63) / 64;
     q.budget = q.splits;
     if (list) {
         const int64_t want = (slabs / kMinSlabs + q.ntm - 1) / q.ntm;
@@ -653,6 +923,13 @@ struct GroupLayout {
     std::vector<int> order;
     std::vector<size_t> off;   // by item
 };
+// room for the ranges of every item's X (an X that two items share takes one)
+size_t range_bytes(const Item *grp, int cnt)
+{
+    size_t n = 0;
+    for (int i = 0; i < cnt; ++i) n += (size_t)((grp[i].in->d + kScanRows - 1) / kScanRows);
+    return align256(sizeof(XRange) * n);
+}
 size_t table_bytes(int cnt) { return align256(sizeof(ErrLayer) * (size_t)cnt); }
 GroupLayout group_layout(const Item *grp, int cnt)
 {
@@ -700,10 +977,11 @@ size_t err_group_scratch_bytes(const ErrLayerIn *in, int n_in, int group)
     return group_bytes(it.data() + base, cnt);
 }
 
-void err_item_d_offsets(const ErrLayerIn *in, int n_in, int64_t *off, int *group)
+void err_item_d_offsets(const ErrLayerIn *in, int n_in, int64_t *off, int64_t *max_off, int *group)
 {
     for (int i = 0; i < n_in; ++i) {
         off[i] = -1;
+        max_off[i] = -1;
         group[i] = -1;
     }
     const std::vector<Item> it = items_of(in, n_in);
@@ -711,14 +989,31 @@ void err_item_d_offsets(const ErrLayerIn *in, int n_in, int64_t *off, int *group
     for (size_t base = 0; base < it.size(); base += kMaxErrItems) {
         const int cnt = (int)std::min<size_t>(kMaxErrItems, it.size() - base);
         const GroupLayout lay = group_layout(it.data() + base, cnt);
-        for (int x = 0; x < cnt; ++x) {
+        int64_t at = (int64_t)range_bytes(it.data() + base, cnt);
+        for (int o = 0; o < cnt; ++o) {   // the maxima lie in launch order
+            const int x = lay.order[o];
             const Item &I = it[base + (size_t)x];
+            const int64_t mine = at;
+            at += 256 * lay.p[x].maxima;
             if (I.use_points != 1) continue;
             const int i = (int)(I.in - in);
             off[i] = (int64_t)lay.off[x];
+            max_off[i] = mine;
             group[i] = (int)(base / kMaxErrItems);
         }
     }
+}
+
+// A second block of a group: the XRange entries, then the row maxima.
+size_t err_group_aux_bytes(const ErrLayerIn *in, int n_in, int group)
+{
+    const std::vector<Item> it = items_of(in, n_in);
+    const size_t base = (size_t)group * kMaxErrItems;
+    if (base >= it.size()) return 0;
+    const int cnt = (int)std::min<size_t>(kMaxErrItems, it.size() - base);
+    size_t b = range_bytes(it.data() + base, cnt);
+    for (int i = 0; i < cnt; ++i) b += 256 * (size_t)((item_rows(*it[base + i].in) + 63) / 64);
+    return b;
 }
 
 double err_group_flop(const ErrLayerIn *in, int n_in, int group)
@@ -731,7 +1026,7 @@ double err_group_flop(const ErrLayerIn *in, int n_in, int group)
 }
 
 hipError_t launch_output_error_group(const ErrLayerIn *in, int n_in, int group, int P, void *scratch,
-                                     hipStream_t s, int parts)
+                                     void *aux, hipStream_t s, int parts)
 {
     const std::vector<Item> it = items_of(in, n_in);
     const size_t base = (size_t)group * kMaxErrItems;
@@ -746,9 +1041,12 @@ hipError_t launch_output_error_group(const ErrLayerIn *in, int n_in, int group, 
         g.n_layers = cnt;
         g.P = P;
         g.vecx = 1;
+        g.xrange = (XRange *)aux;
+        g.rowmax = (uint32_t *)((char *)aux + range_bytes(grp, cnt));
         std::vector<ErrLayer> table(cnt);
-        int64_t blocks = 0, fblocks = 0, nblocks = 0;
+        int64_t blocks = 0, fblocks = 0, nblocks = 0, sblocks = 0, maxima = 0;
         int xoff = 0;
+        std::vector<int> x_begin(n_in, -1);   // a layer's err and ref items share the range of its X
         for (int o = 0; o < cnt; ++o) {
             const int i = order[o];
             const ErrLayerIn &I = *grp[i].in;
@@ -760,14 +1058,14 @@ hipError_t launch_output_error_group(const ErrLayerIn *in, int n_in, int group, 
             L.counts = I.counts;
             L.X = I.X;
             L.out = grp[i].use_points ? I.err : I.ref;
-            L.use_points = grp[i].use_points;
+            L.use_points = (int8_t)grp[i].use_points;
             L.rows = grp[i].use_points == 1 ? I.rows : nullptr;
             L.nrows = grp[i].use_points == 1 ? I.nrows : nullptr;
             L.stride = grp[i].use_points == 1 && I.err_stride > 0 ? I.err_stride : 1;
             L.cand = grp[i].use_points == 2 ? I.cand : nullptr;
             L.offsets = grp[i].use_points == 1 ? I.offsets : nullptr;
             L.Gc = I.Gc;
-            L.M = I.M;
+            L.M = (int8_t)I.M;
             char *cur = (char *)scratch + lay.off[i];
             L.D = (float *)cur;
             cur += q.d_bytes;
@@ -789,12 +1087,25 @@ hipError_t launch_output_error_group(const ErrLayerIn *in, int n_in, int group, 
             blocks += (planned + kXcds - 1) / kXcds * kXcds;
             // the spare tiles (planned % kXcds) of successive layers go to
             // successive XCDs, so no XCD collects one from every layer
-            L.xoff = xoff;
+            L.xoff = (int8_t)xoff;
             xoff = (xoff + (int)(planned % kXcds)) % kXcds;
             L.form_begin = (int)fblocks;
             // rows the fit wrote need no forming
             const bool ready = grp[i].use_points == 1 && I.d_ready && !I.cand;
-            if (!ready) fblocks += ((int64_t)L.C * L.nkb * (kBK / 4) + kFormThreads - 1) / kFormThreads;
+            if (maxima > 0x7fffffffLL) return hipErrorInvalidValue;
+            L.max_begin = (int)maxima;
+            maxima += q.maxima;
+            L.scan_begin = (int)sblocks;
+            int &xb = x_begin[grp[i].in - in];
+            if (xb < 0 && I.d >= kHalfMinD) {
+                xb = (int)sblocks;
+                sblocks += (I.d + kScanRows - 1) / kScanRows;
+            }
+            L.x_begin = xb;
+            if (!ready) {
+                const int64_t rows = kFormThreads / form_lanes((int64_t)L.nkb * (kBK / 4));
+                fblocks += (L.C + rows - 1) / rows;
+            }
             L.fin_begin = (int)nblocks;
             nblocks += q.ypart_bytes ? (L.C + kFinRows - 1) / kFinRows : (L.C + 255) / 256;
             L.vecw = I.d % 4 == 0 && ((uintptr_t)I.W) % 16 == 0 && ((uintptr_t)I.codes) % 4 == 0;
@@ -811,7 +1122,7 @@ hipError_t launch_output_error_group(const ErrLayerIn *in, int n_in, int group, 
             blocks += ((int64_t)L.tiles + kXcds - 1) / kXcds * kXcds -
                       (planned + kXcds - 1) / kXcds * kXcds;
         }
-        if (blocks > 0x7fffffffLL || fblocks > 0x7fffffffLL || nblocks > 0x7fffffffLL)
+        if (blocks > 0x7fffffffLL || fblocks > 0x7fffffffLL || nblocks > 0x7fffffffLL || sblocks > 0x7fffffffLL)
             return hipErrorInvalidValue;
         hipError_t e = hipSuccess;
         // the descriptor table at the head of the group's scratch
@@ -823,6 +1134,11 @@ hipError_t launch_output_error_group(const ErrLayerIn *in, int n_in, int group, 
             for (int i = 0; i < c.count; ++i) c.L[i] = table[o + i];
             LaunchTimer timer(s, "desc_upload_kernel");
             hipLaunchKernelGGL(desc_upload_kernel, dim3(1), dim3(64), 0, s, c);
+            e = hipGetLastError();
+        }
+        if (e == hipSuccess && (parts & kErrScan) && sblocks > 0) {
+            LaunchTimer timer(s, "scan_x_kernel");
+            hipLaunchKernelGGL(scan_x_kernel, dim3((unsigned)sblocks), dim3(256), 0, s, g, (const ErrLayer *)dtab);
             e = hipGetLastError();
         }
         if (e != hipSuccess || !(parts & kErrKernels)) return e;

@@ -1,0 +1,101 @@
+"""The output error on both sides of the rule that chooses the GEMM's operand
+pieces (rows of at least 128, and an X whose features' ranges lie within 2^10,
+take fp16 ones): ranges within, just past and far past it, a row of X of
+zeros, tiny and huge scales, and non-finite values; formed rows (with the reference error), rows the
+fit wrote, and a calibration fit's listed rows."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from gpu_util import gpu_fit, say   # noqa: E402
+from test_gpu_parity import _gpu_err, _oracle_err   # noqa: E402
+
+
+@pytest.fixture(scope="module")
+def orc():
+    import oracle
+    oracle.build()
+    return oracle
+
+
+def _rows(C, d, n, spread, seed):
+    """W, X: feature k of X has largest magnitude 2^e, e from 0 down to -spread; channels that live on
+    the small features only among the others."""
+    rng = np.random.default_rng(seed)
+    W = rng.standard_normal((C, d)).astype(np.float32)
+    X = np.clip(rng.standard_normal((d, n)), -1, 1).astype(np.float32)
+    X[:, 0] = 1.0
+    e = -np.round(np.linspace(0, spread, d))
+    X = (X * np.ldexp(1.0, e.astype(int))[:, None]).astype(np.float32)
+    W[:: 3, : d // 2] *= np.float32(2.0 ** -20)
+    W[1] = 0.0
+    W[1, -1] = 1.0
+    return W, X
+
+
+@pytest.mark.parametrize("C,d,n", [(5, 129, 7), (130, 128, 200), (64, 1600, 130), (9, 127, 1001), (260, 2047, 33)])
+@pytest.mark.parametrize("spread,xs,ws", [(0, 0, 0), (10, 0, 0), (11, 0, 0), (40, 0, 0), (10, -90, 20), (3, 90, -60)])
+def test_against_oracle(orc, C, d, n, spread, xs, ws):
+    say(f"case pieces C={C} d={d} n={n} spread={spread} xs={xs} ws={ws}")
+    W, X = _rows(C, d, n, spread, C + d)
+    X[d // 3] = 0.0
+    W = (W * np.float32(2.0 ** ws)).astype(np.float32)
+    X = (X * np.float32(2.0 ** xs)).astype(np.float32)
+    out = gpu_fit(W, 4, 3, 64, 1e-3)
+    eo, ro = _oracle_err(orc, W, out, X)
+    eg, rg = _gpu_err(W, out, X)
+    # fp32's own range: where the mean square is a normal fp32 value
+    for g, o in ((eg, eo), (rg, ro)):
+        ok = (o > 1e-36) & (o < 1e38)
+        assert np.all(np.abs(g - o)[ok] <= 1e-5 * o[ok]), np.max(np.abs(g - o)[ok] / o[ok])
+
+
+def test_whole_path_and_calibration(orc):
+    """Rows of D from the fit, and listed rows, on both sides of the rule: equal to the error of formed rows."""
+    import torch
+    from paper_2002_09049_amd import mpq
+    shapes = [(70, 12, 200), (130, 600, 200), (40, 2000, 130)]
+    for spread in (4, 30):
+        Ws, Xs = zip(*(_rows(C, d, n, spread, 7 + d) for C, d, n in shapes))
+        say(f"case whole path, spread={spread}")
+        net = mpq.LayerSet([torch.from_numpy(w).cuda() for w in Ws], 3, calib=[torch.from_numpy(x).cuda() for x in Xs])
+        net.quantize(4, 64, 1e-3)
+        torch.cuda.synchronize()
+        for i, (W, X) in enumerate(zip(Ws, Xs)):
+            out = tuple(v[i].cpu().numpy() for v in (net.codes, net.scales, net.counts))
+            eo, _ = orc.output_error(W, *out, X)
+            g = net.err[i].cpu().numpy()
+            assert np.all(np.abs(g - eo) <= 1e-5 * eo)
+        net.fit_calib(4, 64, 1e-3, relative=True)
+        torch.cuda.synchronize()
+        for i, (W, X) in enumerate(zip(Ws, Xs)):
+            codes, scales, counts = (v[i].cpu().numpy() for v in (net.codes, net.scales, net.counts))
+            eo, _ = orc.output_error(W, codes, scales, counts, X)
+            xe = net.xerr[i].cpu().numpy()
+            live = counts > 0
+            last = xe[np.arange(len(counts)), np.maximum(counts - 1, 0)]
+            assert np.all(np.abs(last - eo)[live] <= 1e-5 * eo[live])
+
+
+def test_not_finite():
+    """An infinity or a NaN in a channel or in X gives what the products give: NaN in the rows that meet it."""
+    C, d, n = 40, 200, 100
+    say("case not finite")
+    rng = np.random.default_rng(3)
+    W = rng.standard_normal((C, d)).astype(np.float32)
+    X = rng.standard_normal((d, n)).astype(np.float32)
+    out = gpu_fit(W, 4, 2, 64, 1e-3)
+    good, ref = _gpu_err(W, out, X)
+    W2 = W.copy()
+    W2[3, 5], W2[7, 100] = np.inf, np.nan
+    eg, rg = _gpu_err(W2, out, X)
+    for v, g in ((eg, good), (rg, ref)):
+        assert np.all(np.isnan(v[[3, 7]]))
+        rest = np.delete(np.arange(C), [3, 7])
+        assert np.array_equal(v[rest], g[rest])
+    for bad in (np.inf, np.nan):
+        X2 = X.copy()
+        X2[9, 11] = bad
+        eg, rg = _gpu_err(W, out, X2)
+        assert not np.any(np.isfinite(eg)) and not np.any(np.isfinite(rg))
