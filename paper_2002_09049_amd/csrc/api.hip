@@ -179,9 +179,10 @@ hipError_t fork_pool_init(ForkPool &F)
 
 // Runs launch(j, stream) for the jobs 0..n-1, longest work first, each on the
 // least loaded of the caller's stream and up to kForkStreams pool streams.
-// Falls back to the caller's stream alone when the pool cannot be created.
+// Falls back to the caller's stream alone when the pool cannot be created;
+// serial asks for that (in the same order).
 template <class Launch>
-hipError_t run_concurrently(hipStream_t s, const std::vector<double> &work, Launch launch)
+hipError_t run_concurrently(hipStream_t s, const std::vector<double> &work, Launch launch, bool serial = false)
 {
     const int n = (int)work.size();
     std::vector<int> order(n);
@@ -190,7 +191,7 @@ hipError_t run_concurrently(hipStream_t s, const std::vector<double> &work, Laun
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
-    ForkPool *F = (n > 1 && dev >= 0 && dev < kMaxDevices) ? &g_fork[dev] : nullptr;
+    ForkPool *F = (n > 1 && !serial && dev >= 0 && dev < kMaxDevices) ? &g_fork[dev] : nullptr;
     std::unique_lock<std::mutex> lk;
     if (F) {
         lk = std::unique_lock<std::mutex>(F->mu);
@@ -685,6 +686,7 @@ struct QuantizeStep {
     ErrJobs ej;
     double rec_bytes = 0.0;
     int n_grid = 0, max_points = 0;
+    bool small = false;   // one after the other on the caller's stream
 };
 
 // The checks of mpq_quantize_layers, before any HIP call but the device
@@ -737,6 +739,17 @@ void quantize_build(const mpq_layer *layers, int n_layers, int bits, int max_poi
     int longest = -1;
     for (int i = 0; i < (int)q->jobs.size(); ++i)
         if (longest < 0 || q->jobs[i].work > q->jobs[longest].work) longest = i;
+    // A step of one fit launch over few weights and samples: a fork and a
+    // join cost the host and the queues more than what they would overlap
+    // (scan, upload and reconstruction, a few us each at these sizes).
+    // 64 x 576 weights on 256 samples took 95 us forked and 57 us in turn.
+    constexpr double kSmallWeights = 1 << 20, kSmallBatch = 1 << 21;
+    double weights = 0.0, batch = 0.0;
+    for (int l = 0; l < n_layers; ++l) {
+        weights += (double)layers[l].c_out * (double)layers[l].d;
+        if (layers[l].out_err) batch += (double)layers[l].d * (double)layers[l].n;
+    }
+    q->small = q->jobs.size() == 1 && weights <= kSmallWeights && batch <= kSmallBatch;
     q->rec_after.assign(q->jobs.size(), {});
     std::vector<int> job_of(n_layers, -1);
     for (int i = 0; i < (int)q->jobs.size(); ++i) {
@@ -808,7 +821,7 @@ hipError_t quantize_enqueue(QuantizeStep &q, hipStream_t s)
         for (int g = 0; g < n_groups && e1 == hipSuccess; ++g)
             e1 = launch_err_job(q.err, q.ej, g, q.max_points, st, mpq::kErrUpload | mpq::kErrScan);
         return e1;
-    });
+    }, q.small);
     if (e != hipSuccess) return e;
     // work in GEMM FLOP and, for the reconstruction, bytes (at ~2 TB/s
     // against ~100 TFLOP/s: x 50)
@@ -818,7 +831,7 @@ hipError_t quantize_enqueue(QuantizeStep &q, hipStream_t s)
     return run_concurrently(s, w2, [&](int i, hipStream_t st) {
         return i < n_err_jobs ? launch_err_job(q.err, q.ej, i, q.max_points, st, mpq::kErrKernels)
                               : mpq::launch_reconstruct(q.rec.data(), (int)q.rec.size(), q.max_points, st);
-    });
+    }, q.small);
 }
 
 int quantize_impl(const mpq_layer *layers, int n_layers, int bits, int max_points,

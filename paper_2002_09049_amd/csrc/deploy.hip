@@ -290,7 +290,7 @@ __global__ void __launch_bounds__(kIThreads) int_forward_kernel(const IntGroup g
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
         const int64_t k = ch0 + 8 * (v / 4) + 4 * (lane / 32) + v % 4;
-        if (k < C && col < N) L.Y[k * N + col] = sum[v] >> g.p;
+        if (k < C && col < N) __builtin_nontemporal_store((int64_t)(sum[v] >> g.p), &L.Y[k * N + col]);
     }
 }
 

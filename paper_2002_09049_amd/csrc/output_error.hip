@@ -17,7 +17,7 @@
 //     already wrote (d_ready) are not formed.
 //
 //  2. gemm: Y = D X, the path's one dense contraction, in fp32 from 16-bit
-//     matrix products with fp32 accumulation.  Long rows (d >= kHalfMinD)
+//     matrix products with fp32 accumulation.  Large layers (d >= kHalfMinD, C >= kHalfMinC)
 //     whose X spans a moderate range take three fp16 pieces of D and two of X
 //     and four piece products, on rows of D and an X scaled by powers of two;
 //     the others three bf16 pieces each (hi + mid + lo, exact) and six of the
@@ -41,7 +41,7 @@
 // written to err[rows[m] * stride].  A row's result does not depend on its
 // position, so the list order does not matter.
 //
-//  0. scan (long rows only): the largest |x| of X and the smallest of its
+//  0. scan (large layers only): the largest |x| of X and the smallest of its
 //     rows' maxima, for the choice of the pieces; beside the fits where there
 //     are any.
 //
@@ -87,13 +87,14 @@ constexpr int kStageT = 256;    // threads of the staging wavefronts
 constexpr int kPieces = 3;      // pieces of an fp32 operand (of X with fp16: two)
 constexpr int kSpread = 10;     // fp16 pieces: largest spread of the exponents of X's row maxima
 constexpr int kHalfMinD = 128;  // fp16 pieces: shortest rows
+constexpr int kHalfMinC = 256;  // and fewest channels
 constexpr int kTopExp = 14;     // exponent of an fp16 piece's row or layer maximum after scaling
 constexpr int kSlabK = 16;      // k per staged slab (one 16-k MFMA step)
 constexpr int kRowK = kSlabK + 8;   // LDS row of a piece: 16 bf16 and 16 bytes of padding (48 bytes)
 constexpr int kSlabH = 32;      // k per staged slab of fp16 pieces
 constexpr int kRing = 4;        // staging register sets: loads run four slabs ahead (two fp16 ones)
 constexpr int kMaxErrItems = 1024;   // items (err and ref) per launch group
-constexpr int kDescChunk = 20;       // descriptors per upload kernel
+constexpr int kDescChunk = 22;       // descriptors per upload kernel
 constexpr int kXcds = 8;         // MI355X: workgroups are dealt to 8 XCDs in turn
 constexpr int kFormThreads = 256;
 constexpr int kFinRows = 256 / kWave;   // finish: rows of a split layer per workgroup
@@ -137,7 +138,7 @@ struct ErrLayer {
     int scan_begin;      // first range scan workgroup
     int Gc;
     int max_begin;       // the rows' maxima: ErrGroup::rowmax + 64 max_begin
-    int x_begin;         // the range of X: ErrGroup::xrange[x_begin ..], one per kScanRows rows
+    int x_begin;         // the range of X: ErrGroup::xrange[x_begin ..], one per kScanRows rows; or -1
     int8_t use_points;   // 1: D = residual (err), 0: D = W (ref), 2: D = clipping candidates
     int8_t xoff;         // XCD rank offset: the layer's spare tiles go to XCDs xoff, xoff + 1, ...
     int8_t vecw;         // d % 4 == 0, W 16-byte and codes 4-byte aligned
@@ -457,7 +458,10 @@ __device__ __forceinline__ _Float16 *piece_at(uint16_t *tiles, int buf, int piec
 // 2^-28 of the row's largest product.  A third fewer fp32 additions round off
 // less.  A wider range, a non-finite X or one near fp32's limits take the bf16
 // pieces, as do rows of less than kHalfMinD (nothing to gain: their launches
-// are bound by latency).  Measured, six bf16 products -> four fp16 ones: rms
+// are bound by latency) and layers of less than kHalfMinC channels (the two
+// products saved, 4 C d n FLOP at about 1 PFLOP/s, then take less time than the
+// scan, 4 d n bytes at about 3.5 TB/s: a network of a few such layers went
+// from 132 to 145 us).  Measured, six bf16 products -> four fp16 ones: rms
 // relative error of 512 rows' output error on 256 samples 4.2e-8 -> 3.5e-8
 // (d = 128), 6.9e-8 -> 5.8e-8 (d = 1152); the launch of ResNet-50 330 -> 269 us,
 // of VGG-16 fc 2466 -> 1983 us, of a 999 x 2047 layer and its reference on 1001
@@ -547,7 +551,7 @@ gemm_err_kernel(const ErrGroup g, const ErrLayer *__restrict__ Ls)
 
     // fp16 pieces where X's range allows (see above), its scale 2^(kTopExp - ex)
     uint32_t xtop = 0, xlow = 0;
-    for (int i = L.d >= kHalfMinD ? lane : L.d; i * kScanRows < L.d; i += kWave) {
+    for (int i = L.x_begin >= 0 ? lane : L.d; i * kScanRows < L.d; i += kWave) {   // (-1: not scanned)
         const XRange x = g.xrange[L.x_begin + i];
         xtop = max(xtop, x.top);
         xlow = max(xlow, x.nlow);
@@ -1097,7 +1101,7 @@ hipError_t launch_output_error_group(const ErrLayerIn *in, int n_in, int group, 
             maxima += q.maxima;
             L.scan_begin = (int)sblocks;
             int &xb = x_begin[grp[i].in - in];
-            if (xb < 0 && I.d >= kHalfMinD) {
+            if (xb < 0 && I.d >= kHalfMinD && I.C >= kHalfMinC) {
                 xb = (int)sblocks;
                 sblocks += (I.d + kScanRows - 1) / kScanRows;
             }

@@ -1,5 +1,5 @@
 """The output error on both sides of the rule that chooses the GEMM's operand
-pieces (rows of at least 128, and an X whose features' ranges lie within 2^10,
+pieces (layers of at least 256 rows of at least 128, and an X whose features' ranges lie within 2^10,
 take fp16 ones): ranges within, just past and far past it, a row of X of
 zeros, tiny and huge scales, and non-finite values; formed rows (with the reference error), rows the
 fit wrote, and a calibration fit's listed rows."""
@@ -34,7 +34,7 @@ def _rows(C, d, n, spread, seed):
     return W, X
 
 
-@pytest.mark.parametrize("C,d,n", [(5, 129, 7), (130, 128, 200), (64, 1600, 130), (9, 127, 1001), (260, 2047, 33)])
+@pytest.mark.parametrize("C,d,n", [(256, 129, 7), (300, 128, 200), (257, 1600, 130), (256, 127, 301), (255, 600, 90), (260, 2047, 33)])
 @pytest.mark.parametrize("spread,xs,ws", [(0, 0, 0), (10, 0, 0), (11, 0, 0), (40, 0, 0), (10, -90, 20), (3, 90, -60)])
 def test_against_oracle(orc, C, d, n, spread, xs, ws):
     say(f"case pieces C={C} d={d} n={n} spread={spread} xs={xs} ws={ws}")
@@ -55,7 +55,7 @@ def test_whole_path_and_calibration(orc):
     """Rows of D from the fit, and listed rows, on both sides of the rule: equal to the error of formed rows."""
     import torch
     from paper_2002_09049_amd import mpq
-    shapes = [(70, 12, 200), (130, 600, 200), (40, 2000, 130)]
+    shapes = [(70, 12, 200), (300, 600, 200), (256, 900, 130)]
     for spread in (4, 30):
         Ws, Xs = zip(*(_rows(C, d, n, spread, 7 + d) for C, d, n in shapes))
         say(f"case whole path, spread={spread}")
@@ -67,6 +67,12 @@ def test_whole_path_and_calibration(orc):
             eo, _ = orc.output_error(W, *out, X)
             g = net.err[i].cpu().numpy()
             assert np.all(np.abs(g - eo) <= 1e-5 * eo)
+            # alone (a small step, its launches one after the other): the same bits
+            one = mpq.LayerSet([torch.from_numpy(W).cuda()], 3, calib=[torch.from_numpy(X).cuda()])
+            one.quantize(4, 64, 1e-3)
+            torch.cuda.synchronize()
+            for kind in ("codes", "scales", "counts", "fit_err", "err", "W_hat"):
+                assert torch.equal(getattr(one, kind)[0], getattr(net, kind)[i]), kind
         net.fit_calib(4, 64, 1e-3, relative=True)
         torch.cuda.synchronize()
         for i, (W, X) in enumerate(zip(Ws, Xs)):
@@ -80,7 +86,7 @@ def test_whole_path_and_calibration(orc):
 
 def test_not_finite():
     """An infinity or a NaN in a channel or in X gives what the products give: NaN in the rows that meet it."""
-    C, d, n = 40, 200, 100
+    C, d, n = 256, 200, 100
     say("case not finite")
     rng = np.random.default_rng(3)
     W = rng.standard_normal((C, d)).astype(np.float32)
