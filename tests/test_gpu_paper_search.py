@@ -41,3 +41,22 @@ def test_range_search(orc, d, bits, eta):
     say(f"case paper search d={d} bits={bits} eta={eta}")
     W = _rows(d, 10 * d + bits)
     _ok(orc.verify_paper(W, bits, 3, 0.0, *_fit_paper(W, bits, 3, 0.0, eta), eta=eta))
+
+
+@pytest.mark.parametrize("bits", [2, 3])
+def test_all_weights_at_the_largest_code(orc, bits):
+    """Rows near one magnitude with one large weight, whose best scale saturates every weight, left of all
+    breakpoints."""
+    say(f"case paper search, saturated, bits={bits}")
+    rng = np.random.default_rng(40 + bits)
+    d = 200
+    W = np.empty((5, d), dtype=np.float32)
+    W[0] = rng.choice([-1.0, 1.0], d)
+    W[1] = np.abs(W[0])
+    W[2] = np.float32(0.05) * (1 + np.float32(0.05) * rng.standard_normal(d).astype(np.float32))
+    W[3] = rng.choice([-1.0, 0.0, 1.0], d)
+    W[4] = rng.uniform(1.0, 1.17, d)
+    W[:, 7] = np.float32(12.0 if bits == 2 else 25.0) * np.abs(W).max(1)
+    out = _fit_paper(W, bits, 2, 0.0, 2.0 ** -10)
+    assert (out[2] >= 1).all()
+    _ok(orc.verify_paper(W, bits, 2, 0.0, *out))
