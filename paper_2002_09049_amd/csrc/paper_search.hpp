@@ -211,16 +211,26 @@ __device__ Best paper_search_n(const double *s, const double *S, int d, int dpad
         for (int j = j0 + (t + kT - shift) % kT; j < j1; j += kT) {
             const double b = s[j] / h;
             if (!(b > 0.0)) continue;
-            const long long g0 = (long long)fmin(floor(b / gamma), 4e18);
-            // the first grid point above the breakpoint is the first of the
-            // piece that begins there; the ones at or below it are at most
-            // `fall` less
+            long long g0 = (long long)fmin(floor(b / gamma), 4e18);
+            // The first grid point above the breakpoint, g0 + 1, is the first
+            // of the piece that begins there; the ones at or below it are at
+            // most `fall` less.  Breakpoints often fall on the grid (gamma is
+            // a fraction of a gap), and floor may lose one to a rounding: then
+            // the level's own comparison still has g0 + 1 on the left.  Past
+            // 2^49 grid points even the next one may round onto the
+            // breakpoint: the piece is then entered a little right of it.
+            auto left = [&](long long g) {
+                const double thr = (double)g * gamma * h;
+                return (kl & 1) ? s[j] >= thr : s[j] > thr;
+            };
+            if (left(g0 + 1)) ++g0;
             double E1 = -INFINITY;
-            if (g0 + 1 >= 1 && g0 + 1 <= count) {
+            if (g0 + 1 <= count) {
+                const bool on = left(g0 + 1);
                 double Ag, Bg;
                 int c[kB];
-                E1 = paper_error<kB>(s, S, d, dpad, M, R, (double)(g0 + 1) * gamma, Ag, Bg, c);
-                best = better(best, Best{E1, g0 + 1});
+                E1 = paper_error<kB>(s, S, d, dpad, M, R, on ? b * (1.0 + 0x1p-49) : (double)(g0 + 1) * gamma, Ag, Bg, c);
+                if (!on) best = better(best, Best{E1, g0 + 1});
                 try_vertex(Ag, Bg, c);
             }
             if (!(E1 - fall > fmin(best.e, U) + margin)) {

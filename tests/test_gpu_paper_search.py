@@ -60,3 +60,17 @@ def test_all_weights_at_the_largest_code(orc, bits):
     out = _fit_paper(W, bits, 2, 0.0, 2.0 ** -10)
     assert (out[2] >= 1).all()
     _ok(orc.verify_paper(W, bits, 2, 0.0, *out))
+
+
+@pytest.mark.parametrize("bits", [3, 5])
+def test_grid_points_on_breakpoints(orc, bits):
+    """Magnitudes in a narrow range, their gaps multiples of one spacing, and one large weight: breakpoints that fall
+    on grid points."""
+    say(f"case paper search, breakpoints on the grid, bits={bits}")
+    rng = np.random.default_rng(50 + bits)
+    d = 160
+    W = np.empty((12, d), dtype=np.float32)
+    W[:6] = rng.uniform(1.0, 1.17, (6, d))
+    W[6:] = rng.integers(16, 20, (6, d)) / np.float32(16)
+    W[:, d // 2] = np.float32([12, 16, 25] * 4)
+    _ok(orc.verify_paper(W, bits, 2, 0.0, *_fit_paper(W, bits, 2, 0.0, 2.0 ** -10)))

@@ -82,3 +82,24 @@ def test_all_at_the_largest_code(search, orc):
     for seed in range(40):
         for kind in ("binary", "small", "narrow"):
             check(search, orc, outlier_rows(kind, 100 + seed, seed), 2, [ETA, 2.0 ** -6, 0.3125][seed % 3])
+
+
+def test_grid_points_on_breakpoints(search, orc):
+    """gamma is a fraction of a gap, so that breakpoints fall on grid points, and their quotient a rounding off."""
+    for seed in range(60):
+        d = 150 + 7 * seed % 220
+        for kind in ("narrow", "dyadic", "ternary"):
+            for bits in (3, 4, 5):
+                check(search, orc, outlier_rows(kind, d, 1000 + seed), bits, ETA)
+
+
+def test_other_rows(search, orc):
+    """Ordinary rows, and gaps so small that a grid point's number exceeds a double's precision."""
+    for seed in range(20):
+        for bits in (2, 3, 4, 5, 6):
+            check(search, orc, outlier_rows("normal", 40 + 9 * seed, seed), bits, ETA)
+        r = np.random.default_rng(seed).standard_normal(30 + seed).astype(np.float32).astype(np.float64)
+        r[3] = r[4] * (1 + 2.0 ** -40)
+        r[5] = r[6] + 2.0 ** -48
+        for bits in (2, 3, 5):
+            check(search, orc, r, bits, ETA)
