@@ -42,8 +42,8 @@
 // position, so the list order does not matter.
 //
 //  0. scan (large layers only): the largest |x| of X and the smallest of its
-//     rows' maxima, for the choice of the pieces; beside the fits where there
-//     are any.
+//     rows' mean squares, for the choice of the pieces; beside the fits where
+//     there are any.
 //
 //  3. finish: per row, the partials summed in column-tile order, or the K
 //     ranges of Y summed in range order, squared and summed over the columns;
@@ -85,7 +85,8 @@ constexpr int kMinSlabs = 4;      // shortest K range (slabs) of a listed layer'
 constexpr int kThreads = 512;   // GEMM workgroup: four wavefronts multiply (64 x 64 of the tile each), four stage
 constexpr int kStageT = 256;    // threads of the staging wavefronts
 constexpr int kPieces = 3;      // pieces of an fp32 operand (of X with fp16: two)
-constexpr int kSpread = 10;     // fp16 pieces: largest spread of the exponents of X's row maxima
+constexpr int kSpread = 10;     // fp16 pieces: a row of X has a root mean square of 2^-kSpread of X's largest value or more
+constexpr int kMinExpX = -50;   // and that value an exponent of this or more
 constexpr int kHalfMinD = 128;  // fp16 pieces: shortest rows
 constexpr int kHalfMinC = 256;  // and fewest channels
 constexpr int kTopExp = 14;     // exponent of an fp16 piece's row or layer maximum after scaling
@@ -146,7 +147,8 @@ struct ErrLayer {
 };
 
 // Of kScanRows rows of X: the bits of the largest |x|, and the complement of
-// the bits of the smallest nonzero maximum of |x| over a row.  Kept per
+// the bits of the smallest mean square of a row (0 for one that is not
+// finite).  Kept per
 // workgroup of the scan and reduced by the readers: atomics of many
 // workgroups on one word queue up at the memory side of the XCDs' L2s (they
 // doubled the scan's time).
@@ -196,7 +198,11 @@ __global__ void __launch_bounds__(256) scan_x_kernel(const ErrGroup g, const Err
         if (row >= L.d) break;   // uniform
         const float *x = L.X + row * n;
         uint32_t m = 0;
-        auto add = [&](float v) { m = max(m, __float_as_uint(v) & 0x7fffffffu); };
+        float sq = 0.0f;
+        auto add = [&](float v) {
+            m = max(m, __float_as_uint(v) & 0x7fffffffu);
+            sq = fmaf(v, v, sq);
+        };
         if (vec) {
 #pragma unroll 4
             for (int64_t c = 4 * lane; c < n; c += 4 * kWave) {
@@ -209,8 +215,9 @@ __global__ void __launch_bounds__(256) scan_x_kernel(const ErrGroup g, const Err
         }
 #pragma unroll
         for (int off = kWave / 2; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off));
+        sq = wave_reduce(sq, SumOp()) / (float)n;
         top = max(top, m);
-        if (m != 0) nlow = max(nlow, ~m);
+        nlow = max(nlow, ~(sq < INFINITY ? __float_as_uint(sq) : 0u));
     }
     if (lane == 0) {
         s_top[wid] = top;
@@ -453,10 +460,17 @@ __device__ __forceinline__ _Float16 *piece_at(uint16_t *tiles, int buf, int piec
 // itself left out (Dm Xl), 2^-23 for X's split (exact for three values in
 // four) and 2^-39 of its row's or X's maximum.  The first two change from
 // sample to sample, so a mean over samples hardly sees them; an error of D
-// would be the same in all, hence its third piece.  The last is why X's rows
-// may not differ by more than 2^kSpread in their maxima: then it stays below
-// 2^-28 of the row's largest product.  A third fewer fp32 additions round off
-// less.  A wider range, a non-finite X or one near fp32's limits take the bf16
+// would be the same in all, hence its third piece.  The last (only elements
+// below 2^-15 of their row's maximum lose anything) must not count against
+// the row's output, so the feature that meets the maximum has to be there:
+// every row of X must have a root mean square of 2^-kSpread of X's largest
+// value or more.  Then the row's largest product alone has a root mean square
+// of 2^-kSpread |D|max |X|max, and what d elements lose, 2^-40 |D|max each at
+// random, is 2^-30 sqrt(d) of that at most.  (A rule on the rows' maxima, with
+// zero rows left out, let a large weight on a feature that is dead or hardly
+// ever nonzero hide weights 2^-28 of it, 4e-5 off.)  A third fewer fp32
+// additions round off less.  A row of X with less, a non-finite X or one near
+// fp32's limits take the bf16
 // pieces, as do rows of less than kHalfMinD (nothing to gain: their launches
 // are bound by latency) and layers of less than kHalfMinC channels (the two
 // products saved, 4 C d n FLOP at about 1 PFLOP/s, then take less time than the
@@ -560,7 +574,7 @@ gemm_err_kernel(const ErrGroup g, const ErrLayer *__restrict__ Ls)
     xlow = ~(uint32_t)__builtin_amdgcn_readfirstlane(wave_reduce((int)(xlow ^ 0x80000000u), MaxOp()));
     xlow ^= 0x80000000u;
     const int ex = exponent(xtop);
-    const bool f16 = xtop < 0x7f800000u && ex >= -100 && ex - exponent(xlow) <= kSpread;
+    const bool f16 = xtop < 0x7f800000u && ex >= kMinExpX && exponent(xlow) >= 2 * (ex - kSpread);
     const uint32_t *rmax = g.rowmax + (int64_t)L.max_begin * 64;
     auto row_exp = [&](int64_t r) {   // of a row of D (rows past the live ones: any)
         return r < nact ? max(exponent(rmax[r]), kTopExp - 126) : 0;

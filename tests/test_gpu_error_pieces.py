@@ -1,6 +1,6 @@
 """The output error on both sides of the rule that chooses the GEMM's operand
-pieces (layers of at least 256 rows of at least 128, and an X whose features' ranges lie within 2^10,
-take fp16 ones): ranges within, just past and far past it, a row of X of
+pieces (layers of at least 256 rows of at least 128, and an X whose features' root mean squares lie within 2^10
+of its largest value, take fp16 ones): ranges within, just past and far past it, a row of X of
 zeros, tiny and huge scales, and non-finite values; formed rows (with the reference error), rows the
 fit wrote, and a calibration fit's listed rows."""
 import numpy as np
@@ -105,3 +105,30 @@ def test_not_finite():
         X2[9, 11] = bad
         eg, rg = _gpu_err(W, out, X2)
         assert not np.any(np.isfinite(eg)) and not np.any(np.isfinite(rg))
+
+
+@pytest.mark.parametrize("feature", ["dead", "once"])
+@pytest.mark.parametrize("e", [18, 24, 28])
+def test_large_weights_on_features_that_hardly_occur(feature, e):
+    """Rows whose largest weights sit on features of X that are zero, or nonzero in one sample of many: the other
+    weights, 2^-e of them, make the output error."""
+    import torch
+    from paper_2002_09049_amd import mpq
+    C, d, n = 256, 512, 1024
+    say(f"case rare features {feature} e={e}")
+    rng = np.random.default_rng(e)
+    W = (rng.uniform(0.5, 1.0, (C, d)) * rng.choice([-1.0, 1.0], (C, d)) * 2.0 ** -e).astype(np.float32)
+    X = np.clip(rng.standard_normal((d, n)), -1, 1).astype(np.float32)
+    rare = rng.choice(d, 4, replace=False)
+    W[:, rare] = rng.uniform(0.5, 1.0, (C, 4))
+    X[rare] = 0.0
+    if feature == "once":
+        X[rare, 5 + np.arange(4)] = np.float32(2.0 ** -9)
+    codes = torch.zeros((C, 1, d), dtype=torch.int8, device="cuda")
+    scales = torch.zeros((C, 1), device="cuda")
+    counts = torch.zeros((C,), dtype=torch.int32, device="cuda")
+    err, ref = mpq.output_error(torch.from_numpy(W).cuda(), codes, scales, counts, torch.from_numpy(X).cuda(), with_ref=True)
+    want = ((W.astype(np.float64) @ X.astype(np.float64)) ** 2).mean(1)
+    for got in (err, ref):
+        # fp32 sums of 512 products of random signs, the mean over 1024 samples and one rounding: 2e-7 at most
+        assert np.max(np.abs(got.cpu().numpy() - want) / want) <= 1e-6
