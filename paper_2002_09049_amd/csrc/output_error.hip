@@ -99,7 +99,8 @@ constexpr int kDescChunk = 22;       // descriptors per upload kernel
 constexpr int kXcds = 8;         // MI355X: workgroups are dealt to 8 XCDs in turn
 constexpr int kFormThreads = 256;
 constexpr int kFinRows = 256 / kWave;   // finish: rows of a split layer per workgroup
-constexpr int kScanRows = 16;    // rows of X per workgroup of the range scan
+constexpr int kScanThreads = 256;
+constexpr int kScanMax = 256;    // workgroups of a layer's range scan at most
 
 // Raw buffer resource (gfx9 descriptor word 3: 32-bit dwords, no swizzle).
 // Loads at offsets >= num_records return zeros; kOob is past every range.
@@ -139,14 +140,14 @@ struct ErrLayer {
     int scan_begin;      // first range scan workgroup
     int Gc;
     int max_begin;       // the rows' maxima: ErrGroup::rowmax + 64 max_begin
-    int x_begin;         // the range of X: ErrGroup::xrange[x_begin ..], one per kScanRows rows; or -1
+    int x_begin;         // the range of X: ErrGroup::xrange[x_begin ..], one per scan_rows rows; or -1
     int8_t use_points;   // 1: D = residual (err), 0: D = W (ref), 2: D = clipping candidates
     int8_t xoff;         // XCD rank offset: the layer's spare tiles go to XCDs xoff, xoff + 1, ...
     int8_t vecw;         // d % 4 == 0, W 16-byte and codes 4-byte aligned
     int8_t M;            // levels (at most 127)
 };
 
-// Of kScanRows rows of X: the bits of the largest |x|, and the complement of
+// Of scan_rows rows of X: the bits of the largest |x|, and the complement of
 // the bits of the smallest mean square of a row (0 for one that is not
 // finite).  Kept per
 // workgroup of the scan and reduced by the readers: atomics of many
@@ -182,51 +183,89 @@ __global__ void __launch_bounds__(64) desc_upload_kernel(const DescChunk c)
     for (int i = threadIdx.x; i < c.count * kWords; i += 64) dst[i] = src[i];
 }
 
-// ---- 0. scan: the range of X (see XRange), kScanRows rows per workgroup.
-// Bound by HBM: one read of X, beside the fits where there are any.
-__global__ void __launch_bounds__(256) scan_x_kernel(const ErrGroup g, const ErrLayer *__restrict__ Ls)
+// ---- 0. scan: the range of X (see XRange).  Bound by HBM: one read of X,
+// beside the fits where there are any, else in one launch with the forming of
+// D.  A workgroup takes 16 rows, or one of more than kLongRow samples (few
+// rows of many samples would leave most CUs idle: d = 200 on 100,000 samples
+// by 16 rows cost 128 us more than none, 8 TB/s would be 10), and more where X
+// has many, so that a layer has kScanMax entries at most: every wavefront of
+// the GEMM reads them all.
+constexpr int kLongRow = 4096;
+__host__ __device__ inline int64_t scan_rows(int64_t d, int64_t n)
 {
-    __shared__ uint32_t s_top[4], s_nlow[4];
-    const int li = last_at_most(g.n_layers, (int)blockIdx.x, [&](int i) { return Ls[i].scan_begin; });
+    const int64_t least = n > kLongRow ? 1 : 16, r = (d + kScanMax - 1) / kScanMax;
+    return r > least ? r : least;
+}
+// threads that read a row of n samples: a power of two
+__host__ __device__ inline int scan_lanes(int64_t n)
+{
+    int lanes = n > kLongRow ? kScanThreads : 4;
+    while (lanes < kWave && 4 * lanes < n) lanes *= 2;
+    return lanes;
+}
+__device__ void scan_x(const ErrGroup &g, const ErrLayer *__restrict__ Ls, int block)
+{
+    constexpr int kWaves = kScanThreads / kWave;
+    __shared__ uint32_t s_top[kWaves], s_nlow[kWaves];
+    __shared__ float s_sq[2][kWaves];
+    const int li = last_at_most(g.n_layers, block, [&](int i) { return Ls[i].scan_begin; });
     const ErrLayer &L = Ls[li];
-    const int lane = (int)threadIdx.x % kWave, wid = (int)threadIdx.x / kWave;
-    const int64_t n = L.n;
+    const int t = (int)threadIdx.x, wid = t / kWave;
+    const int64_t n = L.n, rows = scan_rows(L.d, n), row0 = (block - L.scan_begin) * rows;
+    const int lanes = scan_lanes(n), lane = t % lanes, step = kScanThreads / lanes;
     const bool vec = n % 4 == 0 && (uintptr_t)L.X % 16 == 0;
     uint32_t top = 0, nlow = 0;
-    for (int i = wid; i < kScanRows; i += 4) {
-        const int64_t row = (int64_t)((int)blockIdx.x - L.scan_begin) * kScanRows + i;
-        if (row >= L.d) break;   // uniform
-        const float *x = L.X + row * n;
-        uint32_t m = 0;
+    int set = 0;   // two sets of partial sums in turn: one barrier per row
+    for (int64_t i = 0; i < rows; i += step) {   // uniform
+        const int64_t row = row0 + i + t / lanes;
+        const bool live = i + t / lanes < rows && row < L.d;
         float sq = 0.0f;
         auto add = [&](float v) {
-            m = max(m, __float_as_uint(v) & 0x7fffffffu);
+            top = max(top, __float_as_uint(v) & 0x7fffffffu);
             sq = fmaf(v, v, sq);
         };
-        if (vec) {
-#pragma unroll 4
-            for (int64_t c = 4 * lane; c < n; c += 4 * kWave) {
-                const f32x4 v = *(const f32x4 *)(x + c);
-                add(v[0]); add(v[1]); add(v[2]); add(v[3]);
-            }
-        } else {
+        if (live) {
+            const float *x = L.X + row * n;
+            if (vec) {
 #pragma unroll 8
-            for (int64_t c = lane; c < n; c += kWave) add(x[c]);
+                for (int64_t c = 4 * lane; c < n; c += 4 * lanes) {
+                    const f32x4 v = *(const f32x4 *)(x + c);
+                    add(v[0]); add(v[1]); add(v[2]); add(v[3]);
+                }
+            } else {
+#pragma unroll 8
+                for (int64_t c = lane; c < n; c += lanes) add(x[c]);
+            }
         }
+        for (int off = min(lanes, kWave) / 2; off > 0; off >>= 1) sq += __shfl_xor(sq, off);
+        if (lanes > kWave) {   // uniform
+            if (t % kWave == 0) s_sq[set][wid] = sq;
+            __syncthreads();
+            sq = s_sq[set][0];
 #pragma unroll
-        for (int off = kWave / 2; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off));
-        sq = wave_reduce(sq, SumOp()) / (float)n;
-        top = max(top, m);
-        nlow = max(nlow, ~(sq < INFINITY ? __float_as_uint(sq) : 0u));
+            for (int w = 1; w < kWaves; ++w) sq += s_sq[set][w];
+            set ^= 1;
+        }
+        sq /= (float)n;
+        if (live) nlow = max(nlow, ~(sq < INFINITY ? __float_as_uint(sq) : 0u));
     }
-    if (lane == 0) {
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) {
+        top = max(top, (uint32_t)__shfl_xor((int)top, off));
+        nlow = max(nlow, (uint32_t)__shfl_xor((int)nlow, off));
+    }
+    if (t % kWave == 0) {
         s_top[wid] = top;
         s_nlow[wid] = nlow;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        g.xrange[blockIdx.x] = XRange{max(max(s_top[0], s_top[1]), max(s_top[2], s_top[3])),
-                                      max(max(s_nlow[0], s_nlow[1]), max(s_nlow[2], s_nlow[3]))};
+    if (t == 0) {
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) {
+            top = max(top, s_top[w]);
+            nlow = max(nlow, s_nlow[w]);
+        }
+        g.xrange[block] = XRange{top, nlow};
     }
 }
 
@@ -276,15 +315,14 @@ __device__ __forceinline__ int64_t d_index(int64_t m, int64_t k, int nkb)
 // (a power of two from 8 to 256, by its length), so its maximum needs no
 // atomics.
 __device__ __forceinline__ float4 form4(const ErrLayer &L, int P, int64_t m, int64_t k);
-__global__ void __launch_bounds__(kFormThreads) form_d_kernel(const ErrGroup g,
-                                                              const ErrLayer *__restrict__ Ls)
+__device__ void form_d(const ErrGroup &g, const ErrLayer *__restrict__ Ls, int block)
 {
     __shared__ uint32_t s_max[kFormThreads / kWave];
-    const int li = last_at_most(g.n_layers, (int)blockIdx.x, [&](int i) { return Ls[i].form_begin; });
+    const int li = last_at_most(g.n_layers, block, [&](int i) { return Ls[i].form_begin; });
     const ErrLayer &L = Ls[li];
     const int64_t q4 = (int64_t)L.nkb * (kBK / 4);
     const int lanes = form_lanes(q4), t = (int)threadIdx.x;
-    const int64_t m = (int64_t)((int)blockIdx.x - L.form_begin) * (kFormThreads / lanes) + t / lanes;
+    const int64_t m = (int64_t)(block - L.form_begin) * (kFormThreads / lanes) + t / lanes;
     const int64_t nact = L.rows ? (int64_t)*L.nrows : (int64_t)L.C;
     uint32_t top = 0;
     if (m < nact) {   // rows past the list feed only output rows nobody reads
@@ -361,6 +399,22 @@ __device__ __forceinline__ float4 form4(const ErrLayer &L, int P, int64_t m, int
         }
     }
     return make_float4((float)r[0], (float)r[1], (float)r[2], (float)r[3]);
+}
+
+__global__ void __launch_bounds__(kScanThreads) scan_x_kernel(const ErrGroup g, const ErrLayer *__restrict__ Ls)
+{
+    scan_x(g, Ls, (int)blockIdx.x);
+}
+
+// kScan: the scan too, by the first `scans` workgroups
+template <bool kScan>
+__global__ void __launch_bounds__(kFormThreads) form_d_kernel(const ErrGroup g, const ErrLayer *__restrict__ Ls,
+                                                              int scans)
+{
+    static_assert(kScanThreads == kFormThreads, "one launch");
+    const int b = (int)blockIdx.x;
+    if (kScan && b < scans) scan_x(g, Ls, b);
+    else form_d(g, Ls, b - scans);
 }
 
 // ---- 2. gemm: Y = D X, squared and summed per row
@@ -565,10 +619,15 @@ gemm_err_kernel(const ErrGroup g, const ErrLayer *__restrict__ Ls)
 
     // fp16 pieces where X's range allows (see above), its scale 2^(kTopExp - ex)
     uint32_t xtop = 0, xlow = 0;
-    for (int i = L.x_begin >= 0 ? lane : L.d; i * kScanRows < L.d; i += kWave) {   // (-1: not scanned)
-        const XRange x = g.xrange[L.x_begin + i];
-        xtop = max(xtop, x.top);
-        xlow = max(xlow, x.nlow);
+    if (L.x_begin >= 0) {   // (-1: not scanned)
+        const int64_t rows = scan_rows(L.d, n);
+        const int entries = (int)((L.d + rows - 1) / rows);
+#pragma unroll
+        for (int i = 0; i < kScanMax; i += kWave) {
+            const XRange x = i + lane < entries ? g.xrange[L.x_begin + i + lane] : XRange{0u, 0u};
+            xtop = max(xtop, x.top);
+            xlow = max(xlow, x.nlow);
+        }
     }
     xtop = (uint32_t)__builtin_amdgcn_readfirstlane(wave_reduce((int)xtop, MaxOp()));   // no sign bits
     xlow = ~(uint32_t)__builtin_amdgcn_readfirstlane(wave_reduce((int)(xlow ^ 0x80000000u), MaxOp()));
@@ -941,11 +1000,16 @@ struct GroupLayout {
     std::vector<int> order;
     std::vector<size_t> off;   // by item
 };
+size_t scan_entries(const ErrLayerIn &I)
+{
+    const int64_t rows = scan_rows(I.d, I.n);
+    return (size_t)((I.d + rows - 1) / rows);
+}
 // room for the ranges of every item's X (an X that two items share takes one)
 size_t range_bytes(const Item *grp, int cnt)
 {
     size_t n = 0;
-    for (int i = 0; i < cnt; ++i) n += (size_t)((grp[i].in->d + kScanRows - 1) / kScanRows);
+    for (int i = 0; i < cnt; ++i) n += scan_entries(*grp[i].in);
     return align256(sizeof(XRange) * n);
 }
 size_t table_bytes(int cnt) { return align256(sizeof(ErrLayer) * (size_t)cnt); }
@@ -1117,7 +1181,7 @@ hipError_t launch_output_error_group(const ErrLayerIn *in, int n_in, int group, 
             int &xb = x_begin[grp[i].in - in];
             if (xb < 0 && I.d >= kHalfMinD && I.C >= kHalfMinC) {
                 xb = (int)sblocks;
-                sblocks += (I.d + kScanRows - 1) / kScanRows;
+                sblocks += (int64_t)scan_entries(I);
             }
             L.x_begin = xb;
             if (!ready) {
@@ -1154,19 +1218,19 @@ hipError_t launch_output_error_group(const ErrLayerIn *in, int n_in, int group, 
             hipLaunchKernelGGL(desc_upload_kernel, dim3(1), dim3(64), 0, s, c);
             e = hipGetLastError();
         }
-        if (e == hipSuccess && (parts & kErrScan) && sblocks > 0) {
-            LaunchTimer timer(s, "scan_x_kernel");
-            hipLaunchKernelGGL(scan_x_kernel, dim3((unsigned)sblocks), dim3(256), 0, s, g, (const ErrLayer *)dtab);
+        // the scan and the forming in one launch where a call has both now
+        const int scans = (parts & kErrScan) ? (int)sblocks : 0;
+        const int64_t forms = (parts & kErrKernels) ? fblocks : 0;
+        if (scans + forms > 0x7fffffffLL) return hipErrorInvalidValue;
+        if (e == hipSuccess && scans + forms > 0) {
+            const dim3 grid((unsigned)(scans + forms));
+            LaunchTimer timer(s, forms ? "form_d_kernel" : "scan_x_kernel");
+            if (!forms) hipLaunchKernelGGL(scan_x_kernel, grid, dim3(kScanThreads), 0, s, g, (const ErrLayer *)dtab);
+            else hipLaunchKernelGGL(scans ? form_d_kernel<true> : form_d_kernel<false>, grid, dim3(kFormThreads), 0, s,
+                                    g, (const ErrLayer *)dtab, scans);
             e = hipGetLastError();
         }
         if (e != hipSuccess || !(parts & kErrKernels)) return e;
-        if (fblocks > 0) {
-            LaunchTimer timer(s, "form_d_kernel");
-            hipLaunchKernelGGL(form_d_kernel, dim3((unsigned)fblocks), dim3(kFormThreads), 0, s, g,
-                               (const ErrLayer *)dtab);
-            e = hipGetLastError();
-        }
-        if (e != hipSuccess) return e;
         {
             LaunchTimer timer(s, "gemm_err_kernel");
             auto kern = g.vecx ? gemm_err_kernel<true> : gemm_err_kernel<false>;

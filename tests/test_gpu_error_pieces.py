@@ -132,3 +132,34 @@ def test_large_weights_on_features_that_hardly_occur(feature, e):
     for got in (err, ref):
         # fp32 sums of 512 products of random signs, the mean over 1024 samples and one rounding: 2e-7 at most
         assert np.max(np.abs(got.cpu().numpy() - want) / want) <= 1e-6
+
+
+@pytest.mark.parametrize("d,n", [(128, 1), (129, 3), (300, 4), (257, 17), (200, 260), (4097, 65), (131, 4096), (130, 4097),
+                                 (600, 4100), (20000, 12)])
+def test_scan_finds_its_features(orc, d, n):
+    """A feature that the rule must not miss, at each place of the scan's rows and samples: a dead one under the largest
+    weights, a value far past the others."""
+    import torch
+    from paper_2002_09049_amd import mpq
+    C = 256
+    say(f"case scan d={d} n={n}")
+    rng = np.random.default_rng(d + n)
+    X = rng.uniform(0.25, 1.0, (d, n)).astype(np.float32)
+    Wn = (rng.uniform(0.5, 1.0, (C, d)) * 2.0 ** -28).astype(np.float32)
+    codes = torch.zeros((C, 1, d), dtype=torch.int8, device="cuda")
+    scales = torch.zeros((C, 1), device="cuda")
+    counts = torch.zeros((C,), dtype=torch.int32, device="cuda")
+    for j in sorted({0, 1, d // 3, 15, 16, 17, d - 2, d - 1}):
+        W, Xd, Xt = Wn.copy(), X.copy(), X.copy()
+        W[:, j] = 1.0
+        Xd[j] = 0.0
+        for x, w in ((Xd, W), (Xt, Wn)):
+            if w is Wn:
+                x[j, (7 * j) % n] = np.float32(2.0 ** 20)
+            err = mpq.output_error(torch.from_numpy(w).cuda(), codes, scales, counts, torch.from_numpy(x).cuda())
+            if isinstance(err, tuple):
+                err = err[0]
+            # in pieces of samples: sums of positive products, of d terms in fp32
+            want = sum(((w.astype(np.float64) @ x[:, a:a + 4096].astype(np.float64)) ** 2).sum(1) for a in range(0, n, 4096)) / n
+            rel = np.max(np.abs(err.cpu().numpy() - want) / want)
+            assert rel <= 4e-6, (j, w is Wn, rel)
