@@ -532,9 +532,9 @@ int check_error_layer(const mpq_layer &L, int max_points, bool need_x)
     return MPQ_OK;
 }
 
-// Room for a call's row maxima and ranges behind the fixed workspace: a row
-// of D takes at least 128 bytes of it and 4 of these, and a call of one layer
-// has two items, each rounded up to 256 bytes.
+// Room for a call's row maxima and ranges behind the fixed workspace: the
+// maxima take at most a 32nd of what D does, and the ranges of a call's one
+// layer (two items) at most 4096 bytes.
 constexpr size_t kNoallocAux = (size_t)MPQ_NOALLOC_BYTES / 32 + 4096;
 
 // The independent launch groups of an output error, with one scratch block

@@ -214,8 +214,7 @@ struct ErrLayerIn {
 int err_group_count(const ErrLayerIn *in, int n_in);
 size_t err_group_scratch_bytes(const ErrLayerIn *in, int n_in, int group);
 // A second block of each group: the ranges of X and the maxima of D's rows
-// (at most a 32nd of the scratch, half a byte for
-// each of X's rows and 512 bytes per item).
+// (at most a 32nd of the scratch and 2 KiB per item).
 size_t err_group_aux_bytes(const ErrLayerIn *in, int n_in, int group);
 double err_group_flop(const ErrLayerIn *in, int n_in, int group);
 // The parts of a group's launch: the upload of its descriptor table and the

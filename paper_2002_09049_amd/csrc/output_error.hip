@@ -103,8 +103,7 @@ constexpr int kScanThreads = 256;
 constexpr int kScanMax = 256;    // workgroups of a layer's range scan at most
 
 // Raw buffer resource (gfx9 descriptor word 3: 32-bit dwords, no swizzle).
-// Loads at offsets >= num_records return zeros; kOob is past every range.
-constexpr uint32_t kOob = 0x80000000u;
+// Loads at offsets >= num_records return zeros.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *base, uint32_t num_records)
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, (int)num_records,
@@ -139,11 +138,12 @@ struct ErrLayer {
     int fin_begin;       // first finish workgroup
     int scan_begin;      // first range scan workgroup
     int Gc;
-    int max_begin;       // the rows' maxima: ErrGroup::rowmax + 64 max_begin
+    int max_begin;       // the rows' maxima: ErrGroup::rowmax + 64 max_begin, `parts` times [C rounded up to 64]
     int x_begin;         // the range of X: ErrGroup::xrange[x_begin ..], one per scan_rows rows; or -1
-    int8_t use_points;   // 1: D = residual (err), 0: D = W (ref), 2: D = clipping candidates
+    uint8_t use_points : 2,   // 1: D = residual (err), 0: D = W (ref), 2: D = clipping candidates
+        vecw : 1;             // d % 4 == 0, W 16-byte and codes 4-byte aligned
     int8_t xoff;         // XCD rank offset: the layer's spare tiles go to XCDs xoff, xoff + 1, ...
-    int8_t vecw;         // d % 4 == 0, W 16-byte and codes 4-byte aligned
+    int8_t parts;        // pieces of a row that have a maximum each (form_parts; the fit's rows: 1), 0: none
     int8_t M;            // levels (at most 127)
 };
 
@@ -185,23 +185,25 @@ __global__ void __launch_bounds__(64) desc_upload_kernel(const DescChunk c)
 
 // ---- 0. scan: the range of X (see XRange).  Bound by HBM: one read of X,
 // beside the fits where there are any, else in one launch with the forming of
-// D.  A workgroup takes 16 rows, or one of more than kLongRow samples (few
-// rows of many samples would leave most CUs idle: d = 200 on 100,000 samples
-// by 16 rows cost 128 us more than none, 8 TB/s would be 10), and more where X
-// has many, so that a layer has kScanMax entries at most: every wavefront of
-// the GEMM reads them all.
+// D.  Threads in proportion to a row's samples read it, a whole workgroup a
+// row of more than kLongRow (d = 200 on 100,000 samples by 16 rows a workgroup
+// cost 128 us more than no scan, 8 TB/s would be 10).  A workgroup takes one
+// row for each such group of its threads, and more where X has many, so that a
+// layer has kScanMax entries at most: every wavefront of the GEMM reads them
+// all.
 constexpr int kLongRow = 4096;
-__host__ __device__ inline int64_t scan_rows(int64_t d, int64_t n)
-{
-    const int64_t least = n > kLongRow ? 1 : 16, r = (d + kScanMax - 1) / kScanMax;
-    return r > least ? r : least;
-}
 // threads that read a row of n samples: a power of two
 __host__ __device__ inline int scan_lanes(int64_t n)
 {
     int lanes = n > kLongRow ? kScanThreads : 4;
     while (lanes < kWave && 4 * lanes < n) lanes *= 2;
     return lanes;
+}
+// rows of a workgroup
+__host__ __device__ inline int64_t scan_rows(int64_t d, int64_t n)
+{
+    const int64_t step = kScanThreads / scan_lanes(n);
+    return ((d + kScanMax - 1) / kScanMax + step - 1) / step * step;
 }
 __device__ void scan_x(const ErrGroup &g, const ErrLayer *__restrict__ Ls, int block)
 {
@@ -289,6 +291,14 @@ __device__ __forceinline__ LiveSplit live_split(const ErrLayer &L, int64_t nact)
     return LiveSplit{ntm, (L.d + kch - 1) / kch, kch};
 }
 
+// Row maxima (layers that are scanned): a row of q4 float4s is formed in this
+// many pieces.
+constexpr int kFormQuads = 1024, kFormParts = 32;
+__host__ __device__ inline int form_parts(int64_t q4)
+{
+    const int64_t p = (q4 + kFormQuads - 1) / kFormQuads;
+    return p < kFormParts ? (int)p : kFormParts;
+}
 // threads that form a row of q4 float4s
 __host__ __device__ inline int form_lanes(int64_t q4)
 {
@@ -311,9 +321,11 @@ __device__ __forceinline__ int64_t d_index(int64_t m, int64_t k, int nkb)
 }
 
 // ---- 1. form: rows of D, four consecutive k (one float4) at a time, k past d
-// written as zeros, and each row's largest |D|.  A row takes `lanes` threads
-// (a power of two from 8 to 256, by its length), so its maximum needs no
-// atomics.
+// written as zeros.  Where X is scanned, each row's largest |D| too: a row
+// takes `lanes` threads (a power of two from 8 to 256, by its length), so its
+// maximum needs no atomics, or a long one several workgroups with a maximum
+// each (one workgroup a row of 25088 formed 16 rows in 35 us more than a
+// thread per float4; 256 rows of 1,000,000 in 1.4 ms more).
 __device__ __forceinline__ float4 form4(const ErrLayer &L, int P, int64_t m, int64_t k);
 __device__ void form_d(const ErrGroup &g, const ErrLayer *__restrict__ Ls, int block)
 {
@@ -321,12 +333,20 @@ __device__ void form_d(const ErrGroup &g, const ErrLayer *__restrict__ Ls, int b
     const int li = last_at_most(g.n_layers, block, [&](int i) { return Ls[i].form_begin; });
     const ErrLayer &L = Ls[li];
     const int64_t q4 = (int64_t)L.nkb * (kBK / 4);
-    const int lanes = form_lanes(q4), t = (int)threadIdx.x;
-    const int64_t m = (int64_t)(block - L.form_begin) * (kFormThreads / lanes) + t / lanes;
+    const int t = (int)threadIdx.x, b = block - L.form_begin;
     const int64_t nact = L.rows ? (int64_t)*L.nrows : (int64_t)L.C;
+    // rows past the list feed only output rows nobody reads
+    if (L.parts == 0) {
+        const int64_t idx = (int64_t)b * kFormThreads + t, m = idx / q4, q = idx - m * q4;
+        if (m < nact) *(float4 *)(L.D + d_index(m, 4 * q, L.nkb)) = form4(L, g.P, m, 4 * q);
+        return;
+    }
+    const int lanes = form_lanes(q4), part = b % L.parts;
+    const int64_t m = (int64_t)(b / L.parts) * (kFormThreads / lanes) + t / lanes;
+    const int64_t len = (q4 + L.parts - 1) / L.parts, end = min(q4, (part + 1) * len);
     uint32_t top = 0;
-    if (m < nact) {   // rows past the list feed only output rows nobody reads
-        for (int64_t q = t % lanes; q < q4; q += lanes) {
+    if (m < nact) {
+        for (int64_t q = part * len + t % lanes; q < end; q += lanes) {
             const float4 v = form4(L, g.P, m, 4 * q);
             *(float4 *)(L.D + d_index(m, 4 * q, L.nkb)) = v;
             top = max(top, max(max(__float_as_uint(fabsf(v.x)), __float_as_uint(fabsf(v.y))),
@@ -340,7 +360,7 @@ __device__ void form_d(const ErrGroup &g, const ErrLayer *__restrict__ Ls, int b
         const int w0 = t / lanes * (lanes / kWave);
         for (int w = 0; w < lanes / kWave; ++w) top = max(top, s_max[w0 + w]);
     }
-    if (t % lanes == 0 && m < nact) g.rowmax[(int64_t)L.max_begin * 64 + m] = top;
+    if (t % lanes == 0 && m < nact) g.rowmax[L.max_begin * (int64_t)64 + part * ((L.C + (int64_t)63) / 64 * 64) + m] = top;
 }
 
 // D[m][k .. k + 3]
@@ -408,8 +428,8 @@ __global__ void __launch_bounds__(kScanThreads) scan_x_kernel(const ErrGroup g, 
 
 // kScan: the scan too, by the first `scans` workgroups
 template <bool kScan>
-__global__ void __launch_bounds__(kFormThreads) form_d_kernel(const ErrGroup g, const ErrLayer *__restrict__ Ls,
-                                                              int scans)
+__global__ void __launch_bounds__(kFormThreads) __attribute__((amdgpu_waves_per_eu(8))) form_d_kernel(
+    const ErrGroup g, const ErrLayer *__restrict__ Ls, int scans)
 {
     static_assert(kScanThreads == kFormThreads, "one launch");
     const int b = (int)blockIdx.x;
@@ -636,7 +656,10 @@ gemm_err_kernel(const ErrGroup g, const ErrLayer *__restrict__ Ls)
     const bool f16 = xtop < 0x7f800000u && ex >= kMinExpX && exponent(xlow) >= 2 * (ex - kSpread);
     const uint32_t *rmax = g.rowmax + (int64_t)L.max_begin * 64;
     auto row_exp = [&](int64_t r) {   // of a row of D (rows past the live ones: any)
-        return r < nact ? max(exponent(rmax[r]), kTopExp - 126) : 0;
+        if (r >= nact) return 0;
+        uint32_t m = rmax[r];
+        for (int p = 1; p < L.parts; ++p) m = max(m, rmax[p * ((C + 63) / 64 * 64) + r]);
+        return max(exponent(m), kTopExp - 126);
     };
 
     // One barrier per slab for all eight wavefronts: the multiplying ones
@@ -929,10 +952,14 @@ int64_t item_rows(const ErrLayerIn &I) { return I.cand ? I.C * I.Gc : I.C; }
 // an item whose rows are the first *nrows channels of a list
 bool listed(const ErrLayerIn &I, int use_points) { return use_points == 1 && I.rows; }
 
+// fp16 pieces may pay: the range of X is scanned
+bool scanned(const ErrLayerIn &I) { return I.d >= kHalfMinD && I.C >= kHalfMinC; }
+
 struct Plan {
     int64_t nkb, ntm, ntn, splits, kchunk;
     int64_t budget;   // splits of the workgroup budget (ntm * ntn * budget workgroups)
     size_t d_bytes, rowpart_bytes, ypart_bytes;
+    int parts;        // maxima of a row (where X is not scanned, 1 that nobody reads)
     int64_t maxima;   // row maxima, in units of 64
 };
 
@@ -979,7 +1006,8 @@ Plan plan_item(const ErrLayerIn &I, bool list)
     q.splits = (I.d + kchunk - 1) / kchunk;   // no empty K range
     q.d_bytes = align256(sizeof(float) * (size_t)(q.ntm * q.nkb * kBM * kBK));
     q.rowpart_bytes = align256(sizeof(double) * (size_t)(q.ntn * C));
-    q.maxima = (C + 63) / 64;
+    q.parts = scanned(I) ? form_parts(q.nkb * (kBK / 4)) : 1;
+    q.maxima = (C + 63) / 64 * q.parts;
     q.budget = q.splits;
     if (list) {
         const int64_t want = (slabs / kMinSlabs + q.ntm - 1) / q.ntm;
@@ -1002,6 +1030,7 @@ struct GroupLayout {
 };
 size_t scan_entries(const ErrLayerIn &I)
 {
+    if (!scanned(I)) return 0;
     const int64_t rows = scan_rows(I.d, I.n);
     return (size_t)((I.d + rows - 1) / rows);
 }
@@ -1094,7 +1123,10 @@ size_t err_group_aux_bytes(const ErrLayerIn *in, int n_in, int group)
     if (base >= it.size()) return 0;
     const int cnt = (int)std::min<size_t>(kMaxErrItems, it.size() - base);
     size_t b = range_bytes(it.data() + base, cnt);
-    for (int i = 0; i < cnt; ++i) b += 256 * (size_t)((item_rows(*it[base + i].in) + 63) / 64);
+    for (int i = 0; i < cnt; ++i) {
+        const Item &x = it[base + (size_t)i];
+        b += 256 * (size_t)plan_item(*x.in, listed(*x.in, x.use_points)).maxima;
+    }
     return b;
 }
 
@@ -1140,7 +1172,7 @@ hipError_t launch_output_error_group(const ErrLayerIn *in, int n_in, int group, 
             L.counts = I.counts;
             L.X = I.X;
             L.out = grp[i].use_points ? I.err : I.ref;
-            L.use_points = (int8_t)grp[i].use_points;
+            L.use_points = (uint8_t)grp[i].use_points;
             L.rows = grp[i].use_points == 1 ? I.rows : nullptr;
             L.nrows = grp[i].use_points == 1 ? I.nrows : nullptr;
             L.stride = grp[i].use_points == 1 && I.err_stride > 0 ? I.err_stride : 1;
@@ -1179,14 +1211,15 @@ hipError_t launch_output_error_group(const ErrLayerIn *in, int n_in, int group, 
             maxima += q.maxima;
             L.scan_begin = (int)sblocks;
             int &xb = x_begin[grp[i].in - in];
-            if (xb < 0 && I.d >= kHalfMinD && I.C >= kHalfMinC) {
+            if (xb < 0 && scanned(I)) {
                 xb = (int)sblocks;
                 sblocks += (int64_t)scan_entries(I);
             }
             L.x_begin = xb;
+            L.parts = (int8_t)(!scanned(I) ? 0 : ready ? 1 : q.parts);
             if (!ready) {
-                const int64_t rows = kFormThreads / form_lanes((int64_t)L.nkb * (kBK / 4));
-                fblocks += (L.C + rows - 1) / rows;
+                const int64_t q4 = (int64_t)L.nkb * (kBK / 4), rows = kFormThreads / form_lanes(q4);
+                fblocks += L.parts ? (L.C + rows - 1) / rows * L.parts : (L.C * q4 + kFormThreads - 1) / kFormThreads;
             }
             L.fin_begin = (int)nblocks;
             nblocks += q.ypart_bytes ? (L.C + kFinRows - 1) / kFinRows : (L.C + 255) / 256;

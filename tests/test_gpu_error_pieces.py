@@ -163,3 +163,29 @@ def test_scan_finds_its_features(orc, d, n):
             want = sum(((w.astype(np.float64) @ x[:, a:a + 4096].astype(np.float64)) ** 2).sum(1) for a in range(0, n, 4096)) / n
             rel = np.max(np.abs(err.cpu().numpy() - want) / want)
             assert rel <= 4e-6, (j, w is Wn, rel)
+
+
+@pytest.mark.parametrize("C,d", [(256, 4096), (257, 4097), (300, 8224), (256, 140000), (16, 140000), (255, 4100)])
+def test_row_maxima_of_long_rows(C, d):
+    """Rows formed in several pieces, each row's largest weight far past the others and at another place (unseen, its
+    fp16 pieces would overflow); layers whose maxima nobody needs beside them."""
+    import torch
+    from paper_2002_09049_amd import mpq
+    n = 5
+    say(f"case long rows C={C} d={d}")
+    g = torch.Generator(device="cuda").manual_seed(d + C)
+    W = torch.randn((C, d), generator=g, device="cuda")
+    at = (torch.arange(C, device="cuda") * 7919 * 31) % d
+    at[0], at[1], at[2] = 0, d - 1, d // 2
+    W[torch.arange(C, device="cuda"), at] = 2.0 ** 17
+    X = torch.rand((d, n), generator=g, device="cuda") + 0.5
+    codes = torch.zeros((C, 1, d), dtype=torch.int8, device="cuda")
+    codes[:, 0, d // 3] = 3
+    scales = torch.full((C, 1), 0.25, device="cuda")
+    counts = torch.ones((C,), dtype=torch.int32, device="cuda")
+    err, ref = mpq.output_error(W, codes, scales, counts, X, with_ref=True)
+    D = W.double()
+    for got, want in ((ref, (D @ X.double()).square().mean(1)),
+                      (err, ((D - 0.25 * codes[:, 0].double()) @ X.double()).square().mean(1))):
+        # one product of 2^17 among d of random signs: fp32 sums, to a few of its roundings
+        assert ((got.double() - want).abs() / want).max().item() <= 4e-6
