@@ -141,8 +141,9 @@ struct ErrLayer {
     int max_begin;       // the rows' maxima: ErrGroup::rowmax + 64 max_begin, `parts` times [C rounded up to 64]
     int x_begin;         // the range of X: ErrGroup::xrange[x_begin ..], one per scan_rows rows; or -1
     uint8_t use_points : 2,   // 1: D = residual (err), 0: D = W (ref), 2: D = clipping candidates
-        vecw : 1;             // d % 4 == 0, W 16-byte and codes 4-byte aligned
-    int8_t xoff;         // XCD rank offset: the layer's spare tiles go to XCDs xoff, xoff + 1, ...
+        vecw : 1,             // d % 4 == 0, W 16-byte and codes 4-byte aligned
+        xoff : 3;             // XCD rank offset: the layer's spare tiles go to XCDs xoff, xoff + 1, ...
+    uint8_t x_last;      // entries of X's range, less one
     int8_t parts;        // pieces of a row that have a maximum each (form_parts; the fit's rows: 1), 0: none
     int8_t M;            // levels (at most 127)
 };
@@ -601,7 +602,7 @@ gemm_err_kernel(const ErrGroup g, const ErrLayer *__restrict__ Ls)
     const int b = (int)blockIdx.x - (extra ? L.extra_begin : L.block_begin);
     const int xcd = b % kXcds, slot = b / kXcds + (extra ? planned : 0);
     const int q = live / kXcds, rem = live % kXcds;
-    const int xr = (xcd - L.xoff + kXcds) % kXcds;   // the XCD's rank for this layer
+    const int xr = (xcd - (int)L.xoff + kXcds) % kXcds;   // the XCD's rank for this layer
     if (slot >= q + (xr < rem ? 1 : 0)) return;   // padding block
     int tn = xr * q + min(xr, rem) + slot;
     int split = 0, tm = 0;
@@ -640,11 +641,9 @@ gemm_err_kernel(const ErrGroup g, const ErrLayer *__restrict__ Ls)
     // fp16 pieces where X's range allows (see above), its scale 2^(kTopExp - ex)
     uint32_t xtop = 0, xlow = 0;
     if (L.x_begin >= 0) {   // (-1: not scanned)
-        const int64_t rows = scan_rows(L.d, n);
-        const int entries = (int)((L.d + rows - 1) / rows);
 #pragma unroll
-        for (int i = 0; i < kScanMax; i += kWave) {
-            const XRange x = i + lane < entries ? g.xrange[L.x_begin + i + lane] : XRange{0u, 0u};
+        for (int i = 0; i < kScanMax; i += kWave) {   // the loads in flight together
+            const XRange x = g.xrange[L.x_begin + min(i + lane, (int)L.x_last)];
             xtop = max(xtop, x.top);
             xlow = max(xlow, x.nlow);
         }
@@ -658,6 +657,7 @@ gemm_err_kernel(const ErrGroup g, const ErrLayer *__restrict__ Ls)
     auto row_exp = [&](int64_t r) {   // of a row of D (rows past the live ones: any)
         if (r >= nact) return 0;
         uint32_t m = rmax[r];
+#pragma unroll 1
         for (int p = 1; p < L.parts; ++p) m = max(m, rmax[p * ((C + 63) / 64 * 64) + r]);
         return max(exponent(m), kTopExp - 126);
     };
@@ -1201,7 +1201,7 @@ hipError_t launch_output_error_group(const ErrLayerIn *in, int n_in, int group, 
             blocks += (planned + kXcds - 1) / kXcds * kXcds;
             // the spare tiles (planned % kXcds) of successive layers go to
             // successive XCDs, so no XCD collects one from every layer
-            L.xoff = (int8_t)xoff;
+            L.xoff = (uint8_t)xoff;
             xoff = (xoff + (int)(planned % kXcds)) % kXcds;
             L.form_begin = (int)fblocks;
             // rows the fit wrote need no forming
@@ -1216,6 +1216,8 @@ hipError_t launch_output_error_group(const ErrLayerIn *in, int n_in, int group, 
                 sblocks += (int64_t)scan_entries(I);
             }
             L.x_begin = xb;
+            static_assert(kScanMax <= 256, "x_last holds them");
+            L.x_last = (uint8_t)(xb < 0 ? 0 : scan_entries(I) - 1);
             L.parts = (int8_t)(!scanned(I) ? 0 : ready ? 1 : q.parts);
             if (!ready) {
                 const int64_t q4 = (int64_t)L.nkb * (kBK / 4), rows = kFormThreads / form_lanes(q4);
