@@ -106,7 +106,7 @@ hipMemPool_t g_pool[kMaxDevices];
 // MPQ_WORKSPACE_LIMIT (bytes, decimal): a cap on each stream-ordered scratch
 // allocation, checked before any HIP call; a request above it fails as an
 // allocation would (the calls then return MPQ_ERR_NOMEM).  Unset: no cap.
-static bool over_workspace_limit(size_t bytes)
+bool over_workspace_limit(size_t bytes)
 {
     const char *v = getenv("MPQ_WORKSPACE_LIMIT");
     if (!v || !*v) return false;
@@ -115,7 +115,7 @@ static bool over_workspace_limit(size_t bytes)
     return end && *end == '\0' && (unsigned long long)bytes > lim;
 }
 
-hipError_t scratch_alloc(void **p, size_t bytes, hipStream_t s, size_t more)
+hipError_t scratch_alloc(void **p, size_t bytes, hipStream_t s)
 {
     if (over_workspace_limit(bytes)) return hipErrorOutOfMemory;
     int dev = 0;
@@ -138,7 +138,7 @@ hipError_t scratch_alloc(void **p, size_t bytes, hipStream_t s, size_t more)
         }
         pool = g_pool[dev];
     }
-    return hipMallocFromPoolAsync(p, bytes + more == 0 ? 256 : bytes + more, pool, s);
+    return hipMallocFromPoolAsync(p, bytes == 0 ? 256 : bytes, pool, s);
 }
 
 hipError_t scratch_free(void *p, hipStream_t s) { return hipFreeAsync(p, s); }
@@ -545,10 +545,12 @@ struct ErrJobs {
     char *scratch = nullptr;
     char *aux = nullptr;
     bool owned = true;   // allocated by err_jobs (else a caller-held block)
+    bool two = false;    // aux is an allocation of its own
 
     void release(hipStream_t s)
     {
         if (!owned) return;
+        if (two && aux) (void)mpq::scratch_free(aux, s);
         if (scratch) (void)mpq::scratch_free(scratch, s);
         aux = scratch = nullptr;
     }
@@ -581,13 +583,20 @@ int err_jobs(const std::vector<mpq::ErrLayerIn> &in, hipStream_t s, ErrJobs *j,
         j->owned = false;
         return MPQ_OK;
     }
-    // (the limit counts the first block alone, a small share apart)
-    const hipError_t e = mpq::scratch_alloc((void **)&j->scratch, total, s, aux);
+    // both blocks in one allocation, or in two where the workspace limit, a
+    // cap on each, allows no more than the first (aux is the smaller)
+    j->two = mpq::over_workspace_limit(total + aux);
+    hipError_t e = mpq::scratch_alloc((void **)&j->scratch, j->two ? total : total + aux, s);
     if (e != hipSuccess) {
         j->scratch = nullptr;
         return fail(MPQ_ERR_NOMEM, "scratch of %zu bytes: %s", total, hipGetErrorString(e));
     }
     j->aux = j->scratch + total;
+    if (j->two && (e = mpq::scratch_alloc((void **)&j->aux, aux, s)) != hipSuccess) {
+        j->aux = nullptr;
+        j->release(s);
+        return fail(MPQ_ERR_NOMEM, "scratch of %zu bytes: %s", aux, hipGetErrorString(e));
+    }
     return MPQ_OK;
 }
 

@@ -259,8 +259,8 @@ hipError_t launch_clip(const ClipBatch &b, int64_t channels, bool choose, hipStr
 
 // Stream-ordered scratch from a library-owned memory pool of the current
 // device (kept, not returned to the system, between calls).
-// more: bytes that the workspace limit does not count.
-hipError_t scratch_alloc(void **p, size_t bytes, hipStream_t s, size_t more = 0);
+hipError_t scratch_alloc(void **p, size_t bytes, hipStream_t s);
+bool over_workspace_limit(size_t bytes);   // whether it refuses an allocation of that size
 hipError_t scratch_free(void *p, hipStream_t s);
 
 // Reconstruction of Eq. (4) for a list of layers.
