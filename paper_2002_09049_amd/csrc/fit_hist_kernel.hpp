@@ -402,22 +402,39 @@ fit_hist_kernel(const HistBatch B)
         const double q = x * rM;
         return (float)fma(fma(-q, Md, x), rM, q);
     };
-    if constexpr (kMode == kHistGrid) {
-        for (int g = t; g < G; g += T) s_c[g] = B.grid[g];
+    // inclusive prefix sums of p[0 .. n - 1], a run of entries per thread
+    auto prefix_sums = [&](uint16_t *p, int n) {
         sync<T>();
-        // entry i: the multipliers below i / kHistTable less a margin for the
-        // roundings of a query
-        for (int i = t; i <= kHistTable; i += T) {
-            const float y = ((float)i - 0.001f) / (float)kHistTable;
-            int lo = 0, hi = G;
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (s_c[mid] < y) lo = mid + 1;
-                else hi = mid;
-            }
-            s_tab[i] = (uint16_t)lo;
+        const int per = (n + T - 1) / T;
+        const int b0 = min(t * per, n), b1 = min(b0 + per, n);
+        uint32_t tot = 0;
+        for (int b = b0; b < b1; ++b) tot += p[b];
+        uint32_t run = wave_prefix_sum(tot) - tot;
+        if constexpr (kWaves > 1) {
+            if (lane == kWave - 1) s_scan[wid] = run + tot;
+            __syncthreads();
+            for (int w = 0; w < wid; ++w) run += (uint32_t)s_scan[w];
+        }
+        for (int b = b0; b < b1; ++b) {
+            run += p[b];
+            p[b] = (uint16_t)run;
         }
         sync<T>();
+    };
+    if constexpr (kMode == kHistGrid) {
+        // entry i: the multipliers below i / kHistTable less a margin for the
+        // roundings of a query, counted at their first entry and summed up (a
+        // binary search per entry took 5 us)
+        for (int i = t; i < (kHistTable + 2) / 2; i += T) ((uint32_t *)s_tab)[i] = 0;
+        sync<T>();
+        for (int g = t; g < G; g += T) {
+            const float c = B.grid[g];
+            s_c[g] = c;
+            int i = (int)(c * (float)kHistTable);
+            while (i <= kHistTable && !(c < ((float)i - 0.001f) / (float)kHistTable)) ++i;   // at most three steps
+            if (i <= kHistTable) atomicAdd((uint32_t *)s_tab + i / 2, 1u << (16 * (i % 2)));
+        }
+        prefix_sums(s_tab, kHistTable + 1);
     }
     const LatticeShape LS = lattice_shape(T, B.points);
     auto clear_lattice = [&]() {
@@ -444,22 +461,7 @@ fit_hist_kernel(const HistBatch B)
         for (int g = t; g < G; g += T)
 #pragma unroll
             for (int kk = 0; kk < kM; ++kk) s_rank[(2 * kk + 1) * (g + 1)] = 8;
-        sync<T>();
-        const int per = (last + T) / T;   // entries 0 .. last
-        const int b0 = t * per, b1 = min(b0 + per, last + 1);
-        uint32_t tot = 0;
-        for (int b = b0; b < b1; ++b) tot += s_rank[b];
-        uint32_t run = wave_prefix_sum(tot) - tot;
-        if constexpr (kWaves > 1) {
-            if (lane == kWave - 1) s_scan[wid] = run + tot;
-            __syncthreads();
-            for (int w = 0; w < wid; ++w) run += (uint32_t)s_scan[w];
-        }
-        for (int b = b0; b < b1; ++b) {
-            run += s_rank[b];
-            s_rank[b] = (uint16_t)run;
-        }
-        sync<T>();
+        prefix_sums(s_rank, last + 1);
     }
     u64 full = 0;   // linear: the levels every candidate passes
 

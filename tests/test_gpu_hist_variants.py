@@ -56,3 +56,27 @@ def test_sparse_rows(orc):
     W[rng.random(W.shape) < 0.9] = 0.0
     for bits, G in ((4, 256), (8, 128)):
         assert_parity(orc, W, bits, 4, G, 1e-5, gpu_fit(W, bits, 4, G, 1e-5))
+
+
+def _edge_grids(G, rng):
+    """Multipliers on and beside the count table's entries (1024ths), all within one entry, tiny ones."""
+    i = np.sort(rng.choice(np.arange(1, 1025), min(G, 1024), replace=False)).astype(np.float32) / np.float32(1024)
+    yield i
+    yield np.nextafter(i, np.float32(0))
+    up = np.nextafter(i, np.float32(2))
+    yield up[up <= 1]
+    near = ((i * 1024 - np.float32(0.001)) / 1024).astype(np.float32)       # an entry's own value
+    yield np.unique(np.concatenate([near, np.nextafter(near, np.float32(2)), np.nextafter(near, np.float32(0))]))
+    yield np.float32(0.7) + np.arange(G, dtype=np.float32) * np.float32(2.0 ** -24)
+    yield np.unique(np.geomspace(1e-6, 1.0, G).astype(np.float32))
+
+
+@pytest.mark.parametrize("C,d,bits,G", [(3, 40, 4, 1), (4, 300, 2, 65), (5, 200, 8, 300), (2, 1300, 3, 1000), (2, 5000, 4, 130)])
+def test_caller_grid_at_the_table_entries(orc, C, d, bits, G):
+    rng = np.random.default_rng(G)
+    W = (rng.standard_normal((C, d)) * np.exp(rng.standard_normal((C, 1)))).astype(np.float32)
+    for k, grid in enumerate(_edge_grids(G, rng)):
+        grid = np.ascontiguousarray(grid[:4096], dtype=np.float32)
+        say(f"case table grid {k} C={C} d={d} bits={bits} G={grid.size}")
+        out = gpu_fit(W, bits, 3, grid.size, 1e-4, grid=grid)
+        assert_parity(orc, W, bits, 3, grid.size, 1e-4, out, grid=grid)
