@@ -328,13 +328,20 @@ std::vector<FitJob> build_fit_jobs(Search mode, bool hist_fits, const mpq_layer 
                   (L.d <= mpq::kSmallMaxDim ? (double)L.d * (double)n_grid / 24.0 : (double)(L.d + n_grid));
         j.layers.push_back(l);
     };
-    // a call whose channels would leave half of the 1024 SIMDs without a
-    // wavefront gives each channel four (256 x 1152 on a caller's grid: 71 us
-    // against 145 us with one)
-    int64_t waves = 0;
-    for (int l = 0; l < n_layers; ++l)
-        if (layers[l].c_out > 0 && hist(layers[l])) waves += layers[l].c_out * mpq::hist_waves(layers[l].d);
-    const bool wide = waves <= 512;
+    // A call of few channels gives each four wavefronts: up to half of the 1024
+    // SIMDs' number (256 x 1152 on a caller's grid 71 us, with one wavefront
+    // each 145; 512 x 4608, 4 bits, 29 and with two 40), and on a caller's
+    // grid, whose searches wait for LDS, while a wavefront per SIMD is all
+    // there would be (1024 x 576, 4 bits: 53 us and 96).  The default grid's
+    // shorter steps lose there (1024 x 576: 25 us and 23), and both lose with
+    // more (2048 x 576 at 2 bits 39 us and 26, on a caller's grid 67 and 53).
+    int64_t channels = 0, waves = 0;
+    for (int l = 0; l < n_layers; ++l) {
+        if (layers[l].c_out <= 0 || !hist(layers[l])) continue;
+        channels += layers[l].c_out;
+        waves += layers[l].c_out * mpq::hist_waves(layers[l].d);
+    }
+    const bool wide = channels <= 512 || (dgrid && waves <= 1024);
     for (int l = 0; l < n_layers; ++l) {
         const mpq_layer &L = layers[l];
         if (L.c_out == 0 || !hist(L) || !own(L)) continue;
