@@ -758,13 +758,15 @@ fit_hist_kernel(const HistBatch B)
                 });
             } else {
                 miss = (kMode == kHistWide ? 0x1p-21 : 0x1p-45) * sumx + sub;
+                double ia2 = ia;   // grid: opaque (kept from above, the codes spilled 24 registers of 168 at EPT 36)
+                if constexpr (kMode == kHistGrid) asm volatile("" : "+s"(ia2));
                 const double ym = uni((kMode == kHistWide ? GM : (double)kHistTable * Md) * inv_m);
                 each_slot([&](int v, int, int) {
 #pragma unroll
                     for (int c = 0; c < kC; ++c) {
                         const double x = fabs(r[v * kC + c]);
                         const u64 X = (u64)__double_as_longlong(fma(x, scale, 0x1p52)) & ((1ull << 52) - 1);
-                        int kk = (int)top_code(x);   // the levels below are in A0, B0
+                        int kk = (int)fmin(rint(x * ia2), Md);   // top_code: the levels below are in A0, B0
                         const float y = (float)(x * ym);
                         for (; kk < M; ++kk) {
                             const float h = (float)kk + 0.5f;
