@@ -1114,9 +1114,13 @@ int calib_impl(const mpq_layer *layers, int n_layers, int bits, int max_points,
         std::vector<double> w = fit_work;
         const int n_fit = (int)w.size();
         if (step == 0 && !pre) w.insert(w.end(), ej_ref.work.begin(), ej_ref.work.end());
-        // and beside the first step the scan of X's ranges, which all steps use
+        // The scan of X's ranges, which all steps use, runs beside the first
+        // step where that uses every stream anyway, else with the first
+        // forming of D: a stream more to fork and join costs 20 to 35 us (64 x
+        // 576 on 256 samples, absolute threshold: 142 us and 165).
         const int n_ref = (int)w.size() - n_fit;
-        if (step == first) w.resize(w.size() + ej.work.size(), 0.0);
+        const bool scan_beside = n_fit + n_ref > kForkStreams;
+        if (step == first && scan_beside) w.resize(w.size() + ej.work.size(), 0.0);
         e = run_concurrently(s, w, [&](int i, hipStream_t st) {
             if (i < n_fit) return launch_fit_job(jobs[i], n_grid, st);
             if (i < n_fit + n_ref) return launch_err_job(in_ref, ej_ref, i - n_fit, P, st);
@@ -1135,7 +1139,8 @@ int calib_impl(const mpq_layer *layers, int n_layers, int bits, int max_points,
             }
         }
         e = run_concurrently(s, ej.work, [&](int i, hipStream_t st) {
-            return launch_err_job(in_s, ej, i, P, st, mpq::kErrUpload | mpq::kErrKernels);
+            return launch_err_job(in_s, ej, i, P, st, mpq::kErrUpload | mpq::kErrKernels |
+                                                          (step == first && !scan_beside ? mpq::kErrScan : 0));
         });
     }
     release();
