@@ -52,7 +52,8 @@ int device_lds_limit(size_t *bytes)
         int v = 0;
         e = hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
         if (e != hipSuccess) return hip_fail(e, "hipDeviceGetAttribute(MaxSharedMemoryPerBlock)");
-        // the fit kernels also hold ~1 KiB of static LDS
+        // the dense fit also holds ~1 KiB of static LDS (the histogram fit up to
+        // 9 KiB, beside less than 90 KiB of its own at the largest grid)
         g_lds_limit[dev] = v > 2048 ? (size_t)v - 2048 : 1;
     }
     *bytes = g_lds_limit[dev];

@@ -32,6 +32,16 @@ constexpr Variant kWide[] = {{256, 4, true}, {256, 8, true}, {256, 12, true}, {2
 constexpr int kNumWide = sizeof(kWide) / sizeof(kWide[0]);
 constexpr int64_t kWideMinDim = 256;
 
+// as the kernel takes it from the elements per thread
+template <size_t kN>
+constexpr bool quads_as_kernel(const Variant (&v)[kN])
+{
+    for (const Variant &x : v)
+        if (x.quad != (x.ept >= 4) || (x.quad && x.ept % 4 != 0)) return false;
+    return true;
+}
+static_assert(quads_as_kernel(kVariants) && quads_as_kernel(kWide), "groups of four");
+
 // Lattice buckets of LDS at most (8 bytes each).
 constexpr int kLatMaxBuckets = 7680;
 

@@ -189,15 +189,11 @@ fit_hist_kernel(const HistBatch B)
     constexpr int kC = EPT >= 4 ? 4 : 1;
     constexpr int kSlots = EPT / kC;
     static_assert(EPT % kC == 0, "whole groups");
-    // wavefronts that evaluate the candidates (the others wait; with many
-    // wavefronts the candidates are spread over all of them)
-    constexpr int kEvalWaves = 1;
 
     extern __shared__ __align__(16) char hsmem[];
     __shared__ double s_red[2][kWaves];      // per-wave maxima, two sets in turn
     __shared__ double s_part[kWaves > 1 ? 2 : 1][kWaves > 4 ? kWaves : 4][kWaves > 1 ? kWave : 1];   // partial sums
     __shared__ u64 s_scan[kWaves];
-    __shared__ Lead s_lead[kEvalWaves];
     __shared__ int s_pick[2];                // the chosen candidate, whether there are finalists
     __shared__ int s_nfin, s_fin[kMaxFinalists];
 
@@ -806,7 +802,7 @@ fit_hist_kernel(const HistBatch B)
             if constexpr (kMode == kHistLattice) {
                 const char *base = (const char *)(lat + kHistDump + LS.pad - 1);
 #pragma unroll 1
-                for (int g = t; g < G; g += kEvalWaves * kWave) {
+                for (int g = t; g < G; g += kWave) {
                     u64 A = 0;
                     uint32_t Bc = 0;
 #pragma unroll
@@ -868,7 +864,7 @@ fit_hist_kernel(const HistBatch B)
         int gstar = -1;
         bool other = false;   // uniform: a second candidate may be the best
         double thr = INFINITY;
-        if (wid < kEvalWaves) {
+        if (wid == 0) {   // one wavefront evaluates the candidates, the others wait
             if (t == 0) s_nfin = 0;
             if constexpr (kMode == kHistLinear) {   // the lanes' own bins
                 const u64 mine = lane > 0 ? ha[G + lane] : 0;   // bin G is the last candidate's
@@ -886,29 +882,9 @@ fit_hist_kernel(const HistBatch B)
             gm = __builtin_amdgcn_readfirstlane(gm);
             // the other candidates' least lower bound
             const double rest = L.g == gm ? L.rest : fmin(L.rest, L.lb);
-            if constexpr (kEvalWaves > 1) {
-                const double least = wave_reduce(rest, MinOp());
-                if (lane == 0) s_lead[wid] = Lead{emin, emin, least, gm};
-            } else {
-                gstar = emin == INFINITY ? -1 : gm;
-                if (gstar >= 0) thr = fma((double)cand(gstar), c2, uni(emin)) + tiny;
-                other = gstar >= 0 && __builtin_amdgcn_ballot_w64(rest <= thr) != 0;
-            }
-        }
-        if constexpr (kEvalWaves > 1) {
-            __syncthreads();
-            Lead L = s_lead[0];
-#pragma unroll
-            for (int w = 1; w < kEvalWaves; ++w) {
-                const Lead o = s_lead[w];
-                L.rest = fmin(L.rest, o.rest);
-                lead_add(L, o.e, o.lb, o.g);
-            }
-            gstar = __builtin_amdgcn_readfirstlane(L.e == INFINITY ? -1 : L.g);
-            if (gstar >= 0) thr = fma((double)cand(gstar), c2, uni(L.e)) + tiny;
-            // (a wave's own best enters with its error as lower bound: one
-            // candidate's slack, a c2, at most below it)
-            other = gstar >= 0 && uni(L.rest) - (double)m * rM * c2 <= thr;
+            gstar = emin == INFINITY ? -1 : gm;
+            if (gstar >= 0) thr = fma((double)cand(gstar), c2, uni(emin)) + tiny;
+            other = gstar >= 0 && __builtin_amdgcn_ballot_w64(rest <= thr) != 0;
         }
         // the finalists' list (rarely more than the best one)
         auto list_finalists = [&]() {
@@ -919,8 +895,8 @@ fit_hist_kernel(const HistBatch B)
                 }
             });
         };
-        if (other && wid < kEvalWaves) list_finalists();
-        if constexpr (kWaves > 1 && kEvalWaves == 1) {
+        if (other && wid == 0) list_finalists();
+        if constexpr (kWaves > 1) {
             if (t == 0) {
                 s_pick[0] = gstar;
                 s_pick[1] = other ? 1 : 0;

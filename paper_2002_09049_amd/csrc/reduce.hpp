@@ -251,10 +251,8 @@ __device__ __forceinline__ T block_reduce(T v, Op op, T *scratch)
 }
 
 // max of a float and sum of a double over the workgroup, with one pair of
-// barriers (kTrail = false: the first barrier only; the caller then passes
-// another barrier before scratch_f / scratch_d are written again).
-// scratch_f / scratch_d hold one value per wavefront.
-template <int kThreads, bool kTrail = true>
+// barriers.  scratch_f / scratch_d hold one value per wavefront.
+template <int kThreads>
 __device__ __forceinline__ void block_max_sum(float &vmax, double &vsum, float *scratch_f,
                                               double *scratch_d)
 {
@@ -275,41 +273,13 @@ __device__ __forceinline__ void block_max_sum(float &vmax, double &vsum, float *
             m = MaxOp()(m, scratch_f[i]);
             sm = SumOp()(sm, scratch_d[i]);
         }
-        if constexpr (kTrail) __syncthreads();
+        __syncthreads();
         vmax = m;
         vsum = sm;
     }
 }
 
-// two sums of doubles over the workgroup, with one pair of barriers; fixed
-// order.  scratch_a / scratch_b hold one value per wavefront.
 template <int kThreads>
-__device__ __forceinline__ void block_sum2(double &a, double &b, double *scratch_a, double *scratch_b)
-{
-    constexpr int kWaves = kThreads / kWave;
-    a = wave_reduce(a, SumOp());
-    b = wave_reduce(b, SumOp());
-    if constexpr (kWaves > 1) {
-        const int wid = threadIdx.x / kWave;
-        if ((threadIdx.x % kWave) == 0) {
-            scratch_a[wid] = a;
-            scratch_b[wid] = b;
-        }
-        __syncthreads();
-        double x = scratch_a[0], y = scratch_b[0];
-#pragma unroll
-        for (int i = 1; i < kWaves; ++i) {
-            x += scratch_a[i];
-            y += scratch_b[i];
-        }
-        __syncthreads();
-        a = x;
-        b = y;
-    }
-}
-
-// kTrail = false: the first barrier only (as block_max_sum)
-template <int kThreads, bool kTrail = true>
 __device__ __forceinline__ ArgMin block_argmin(ArgMin v, ArgMin *scratch)
 {
     constexpr int kWaves = kThreads / kWave;
@@ -320,7 +290,7 @@ __device__ __forceinline__ ArgMin block_argmin(ArgMin v, ArgMin *scratch)
     ArgMin r = scratch[0];
 #pragma unroll
     for (int i = 1; i < kWaves; ++i) r = argmin_combine(r, scratch[i]);
-    if constexpr (kTrail) __syncthreads();
+    __syncthreads();
     return r;
 }
 

@@ -39,3 +39,19 @@ def test_quad_rows_land_in_their_row(T, EPT):
             j = (j0[:, None] + np.arange(4)).ravel()
             assert sorted(j.tolist()) == list(range(32 * nkb))  # the row and its padding, once
             assert np.array_equal(addr, tiled_slot(k, j, nkb))
+
+
+def test_every_variant_has_its_kernels():
+    """Each mode's source lists every variant that the dispatch can choose with it: all of them, for the lattice those
+    of at least 1024 elements."""
+    text = open(SRC).read()
+    table = [(int(t), int(e)) for name in ("kVariants", "kWide")
+             for t, e in re.findall(r"\{\s*(\d+)\s*,\s*(\d+)\s*,", re.search(name + r"\[\]\s*=\s*\{(.*?)\};", text, re.S).group(1))]
+    assert len(table) == 16 and "cap >= 1024" in text
+    for mode in ("grid", "wide", "linear1", "linear3", "linear7", "lattice1", "lattice3", "lattice7", "lattice15"):
+        src = open(SRC.replace("fit_hist.hip", f"fit_hist_{mode}.hip")).read()
+        name, levels = re.fullmatch(r"([a-z]+)(\d*)", mode).groups()
+        got = re.findall(r"if \(T == (\d+) && ept == (\d+)\) return launch_hist_t<(\d+), (\d+), kHist(\w+), (\d+)>", src)
+        assert all((t, e) == (t2, e2) and m.lower() == name and k == (levels or "0") for t, e, t2, e2, m, k in got)
+        want = [v for v in table if name != "lattice" or v[0] * v[1] >= 1024]
+        assert sorted((int(t), int(e)) for t, e, *_ in got) == sorted(want), mode
