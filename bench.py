@@ -56,10 +56,10 @@ PEAK_HBM_GBS = 8000.0
 PEAK_MFMA_BF16_TFLOPS = 2500.0          # dense bf16 and fp16 MFMA
 
 
-def piece_products(C, d):
-    """16-bit products per fp32 product of the error GEMM on rows of d: four of fp16 pieces (a calibration
-    batch of moderate range, as the workloads' are), six of bf16 ones for short rows and few channels."""
-    return 4 if d >= 128 and C >= 256 else 6
+def piece_products(C, d, n):
+    """16-bit products per fp32 product of the error GEMM on rows of d and n samples: four of fp16 pieces (a
+    calibration batch of moderate range, as the workloads' are), six of bf16 ones for short rows and few channels."""
+    return 4 if d >= 128 and C >= (384 if d * n > 3 << 20 else 256) else 6
 PEAK_VALU_F32_TFLOPS = 157.3            # published (packed) FP32 vector peak
 PEAK_MFMA_I8_TOPS = 5000.0              # dense int8 MFMA
 PEAK_VALU_F32_NONPACKED_TFLOPS = 78.6   # 256 CU x 64 lanes x 2 FLOP x 2.4 GHz
@@ -589,7 +589,7 @@ def main():
             code_reads = int((cnt * (cnt - 1) // 2).sum())
             searched = n - int((cnt > 0).sum()) if args.clip else n
             add(fk, evals=searched * wk.n_grid * d, bytes=4 * n * d + code_reads * d + n * d)
-            add("gemm_err_kernel", flop=2 * (n + C) * d * N, mfma=piece_products(C, d) * 2 * (n + C) * d * N)
+            add("gemm_err_kernel", flop=2 * (n + C) * d * N, mfma=piece_products(C, d, N) * 2 * (n + C) * d * N)
             add("form_d_kernel", bytes=8 * (n + C) * d + (n + code_reads) * d)
         else:
             # fit: G candidate errors per (element, point); reads W once, writes the codes
@@ -599,14 +599,14 @@ def main():
             searched = n - int((cnt > 0).sum()) if args.clip else n
             fit_writes_d = not separate and not args.dense
             add(fk, evals=searched * wk.n_grid * d, bytes=4 * C * d + n * d + (4 * C * d if fit_writes_d else 0))
-            add("gemm_err_kernel", flop=2 * C * d * N, mfma=piece_products(C, d) * 2 * C * d * N)
+            add("gemm_err_kernel", flop=2 * C * d * N, mfma=piece_products(C, d, N) * 2 * C * d * N)
             # form: reads W and the codes of the used points, writes D
             if not fit_writes_d:
                 add("form_d_kernel", bytes=4 * C * d + n * d + 4 * C * d)
         if args.clip:
             # the clipping pass: output errors of C * GC candidate rows
             add("gemm_err_kernel", flop=2 * C * args.clip * d * N,
-                mfma=piece_products(C, d) * 2 * C * args.clip * d * N)
+                mfma=piece_products(C, d, N) * 2 * C * args.clip * d * N)
             add("form_d_kernel", bytes=4 * C * d + 4 * C * args.clip * d)
         # reconstruct: reads the codes of the used points, writes fp32
         add("reconstruct_kernel", bytes=n * d + 4 * C * d)
@@ -707,7 +707,7 @@ def main():
                 "traffic": None if traffic is None else int(traffic),
                 "avg_launch_us": round(K["avg_us"], 3),
                 "fp32_equivalent_tflops": round(K.get("fp32_equivalent_tflops", 0.0), 4),
-                "achieved_is": "4 x 2 C d n fp16 FLOP per layer, 6 x in bf16 for d < 128 or C < 256 (the piece products "
+                "achieved_is": "4 x 2 C d n fp16 FLOP per layer, 6 x in bf16 for d < 128 or few channels (the piece products "
                                "for each of Eq. (12)'s fp32 products) / event-timed launch duration, against "
                                "the dense 16-bit MFMA peak"}
     # the candidate search: the fit kernel with the most time per step, with

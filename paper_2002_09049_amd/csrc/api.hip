@@ -759,7 +759,9 @@ void quantize_build(const mpq_layer *layers, int n_layers, int bits, int max_poi
     // A step of one fit launch over few weights and samples: a fork and a
     // join cost the host and the queues more than what they would overlap
     // (scan, upload and reconstruction, a few us each at these sizes).
-    // 64 x 576 weights on 256 samples took 95 us forked and 57 us in turn.
+    // 64 x 576 weights on 256 samples took 98 us forked and 55 us in turn, at the
+    // limits 1024 x 1024 on 2048 89 and 81; past them the gain goes (1024 x 2048
+    // on 2048 106 both, 1024 x 4608 on 1024 131 and 132).
     constexpr double kSmallWeights = 1 << 20, kSmallBatch = 1 << 21;
     double weights = 0.0, batch = 0.0;
     for (int l = 0; l < n_layers; ++l) {

@@ -88,7 +88,9 @@ constexpr int kPieces = 3;      // pieces of an fp32 operand (of X with fp16: tw
 constexpr int kSpread = 10;     // fp16 pieces: a row of X has a root mean square of 2^-kSpread of X's largest value or more
 constexpr int kMinExpX = -50;   // and that value an exponent of this or more
 constexpr int kHalfMinD = 128;  // fp16 pieces: shortest rows
-constexpr int kHalfMinC = 256;  // and fewest channels
+constexpr int kHalfMinC = 256;  // and fewest channels,
+constexpr int kHalfManyC = 384; // for an X past
+constexpr int64_t kHalfManyX = 3 << 20;   // this many values
 constexpr int kTopExp = 14;     // exponent of an fp16 piece's row or layer maximum after scaling
 constexpr int kSlabK = 16;      // k per staged slab (one 16-k MFMA step)
 constexpr int kRowK = kSlabK + 8;   // LDS row of a piece: 16 bf16 and 16 bytes of padding (48 bytes)
@@ -545,12 +547,16 @@ __device__ __forceinline__ _Float16 *piece_at(uint16_t *tiles, int buf, int piec
 // zero rows left out, let a large weight on a feature that is dead or hardly
 // ever nonzero hide weights 2^-28 of it, 4e-5 off.)  A third fewer fp32
 // additions round off less.  A row of X with less, a non-finite X or one near
-// fp32's limits take the bf16
-// pieces, as do rows of less than kHalfMinD (nothing to gain: their launches
-// are bound by latency) and layers of less than kHalfMinC channels (the two
-// products saved, 4 C d n FLOP at about 1 PFLOP/s, then take less time than the
-// scan, 4 d n bytes at about 3.5 TB/s: a network of a few such layers went
-// from 132 to 145 us).  Measured, six bf16 products -> four fp16 ones: rms
+// fp32's limits take the bf16 pieces, as do rows of less than kHalfMinD
+// (nothing to gain: their launches are bound by latency) and layers of few
+// channels: the two products saved, 4 C d n FLOP at about 1 PFLOP/s, then take
+// less time than the scan, 4 d n bytes at about 3.5 TB/s (128 channels of 4608
+// on 2048 samples: 67.4 us and with bf16 pieces 58.1).  A small X is scanned in
+// the shadow of the launches, so that 256 channels are enough (of 2304 on 1024
+// samples: 49.8 us, bf16 50.9); past kHalfManyX it takes 384 (of 4608 on 2048
+// samples, err alone and with ref: 84.7 and 114 us, bf16 80.6 and 120; 256
+// channels 70.5 and 87.1, bf16 61.8 and 84.2).
+// Measured, six bf16 products -> four fp16 ones: rms
 // relative error of 512 rows' output error on 256 samples 4.2e-8 -> 3.5e-8
 // (d = 128), 6.9e-8 -> 5.8e-8 (d = 1152); the launch of ResNet-50 330 -> 269 us,
 // of VGG-16 fc 2466 -> 1983 us, of a 999 x 2047 layer and its reference on 1001
@@ -953,7 +959,10 @@ int64_t item_rows(const ErrLayerIn &I) { return I.cand ? I.C * I.Gc : I.C; }
 bool listed(const ErrLayerIn &I, int use_points) { return use_points == 1 && I.rows; }
 
 // fp16 pieces may pay: the range of X is scanned
-bool scanned(const ErrLayerIn &I) { return I.d >= kHalfMinD && I.C >= kHalfMinC; }
+bool scanned(const ErrLayerIn &I)
+{
+    return I.d >= kHalfMinD && I.C >= (I.d * I.n > kHalfManyX ? kHalfManyC : kHalfMinC);
+}
 
 struct Plan {
     int64_t nkb, ntm, ntn, splits, kchunk;

@@ -1,5 +1,5 @@
 """The output error on both sides of the rule that chooses the GEMM's operand
-pieces (layers of at least 256 rows of at least 128, and an X whose features' root mean squares lie within 2^10
+pieces (layers of at least 256 rows, 384 for a large X, of at least 128, and an X whose features' root mean squares lie within 2^10
 of its largest value, take fp16 ones): ranges within, just past and far past it, a row of X of
 zeros, tiny and huge scales, and non-finite values; formed rows (with the reference error), rows the
 fit wrote, and a calibration fit's listed rows."""
@@ -223,3 +223,15 @@ def test_workspace_limit_at_the_scratch(monkeypatch):
         got = call()
         monkeypatch.delenv("MPQ_WORKSPACE_LIMIT")
         assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+@pytest.mark.parametrize("C", [255, 256, 383, 384])
+@pytest.mark.parametrize("d,n", [(768, 4096), (769, 4096)])
+def test_channels_where_the_pieces_change(orc, C, d, n):
+    """Both sides of the fewest channels that take fp16 pieces, for X of 3 2^20 values and of more."""
+    say(f"case fewest channels C={C} d={d} n={n}")
+    W, X = _rows(C, d, n, 4, C + d)
+    out = gpu_fit(W, 4, 2, 64, 1e-3)
+    eo, ro = _oracle_err(orc, W, out, X)
+    eg, rg = _gpu_err(W, out, X)
+    assert np.all(np.abs(eg - eo) <= 1e-5 * eo) and np.all(np.abs(rg - ro) <= 1e-5 * ro)
