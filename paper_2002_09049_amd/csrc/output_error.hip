@@ -344,9 +344,14 @@ __device__ void form_d(const ErrGroup &g, const ErrLayer *__restrict__ Ls, int b
         if (m < nact) *(float4 *)(L.D + d_index(m, 4 * q, L.nkb)) = form4(L, g.P, m, 4 * q);
         return;
     }
-    const int lanes = form_lanes(q4), part = b % L.parts;
-    const int64_t m = (int64_t)(b / L.parts) * (kFormThreads / lanes) + t / lanes;
-    const int64_t len = (q4 + L.parts - 1) / L.parts, end = min(q4, (part + 1) * len);
+    const int lanes = form_lanes(q4);
+    int rows = b, part = 0;   // uniform
+    if (L.parts > 1) {
+        rows = b / L.parts;
+        part = b - rows * L.parts;
+    }
+    const int64_t m = (int64_t)rows * (kFormThreads / lanes) + t / lanes;
+    const int64_t len = L.parts > 1 ? ((int)q4 + L.parts - 1) / L.parts : q4, end = min(q4, (part + 1) * len);
     uint32_t top = 0;
     if (m < nact) {
         for (int64_t q = part * len + t % lanes; q < end; q += lanes) {
