@@ -287,7 +287,7 @@ __global__ void __launch_bounds__(kIThreads) int_forward_kernel(const IntGroup g
 
     // Step 3 and the stores: a store writes two 32-column runs of Y rows,
     // non-temporal (Y is 8 bytes an output, read by nobody here: kept out of
-    // the L2s, which hold X and the codes; ResNet-50 on 8 images 577 -> 565 us)
+    // the L2s, which hold X and the codes; ResNet-50 on 8 images 572 -> 559 us)
     const int64_t col = col0 + wid * 32 + lane % 32;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {

@@ -43,10 +43,12 @@
 //
 // One workgroup of T threads per channel, the fp64 residual in registers for
 // the whole fit (EPT elements per thread), so a step reads nothing from HBM.
-// What bounds the kernel is VALU issue (the SIMDs' VALU is 90% busy on the
-// linear mode's 512-long channels) and, with few wavefronts in flight, the
-// latency of a step's serial phases.  An element costs about 20 instructions
-// a step (codes and residual 12, lattice bin 8), a wavefront about 600 more
+// What bounds the kernel is VALU issue (the SIMDs' VALU is 84% busy on the
+// linear mode's channels of 256 weights and 76% on those of 512, 50% on the
+// lattice mode's) and, with few wavefronts in flight, the latency of a step's
+// serial phases.  By the instructions of ResNet-50's launches (3.1 points a
+// channel) an element costs about 40 a step in the lattice mode and 85 in the
+// linear one at 7 levels, a wavefront about 500 and 350 more
 // (reductions, scan, candidates), so a channel takes as few wavefronts as its
 // registers allow: one up to 1280 elements, without barriers.  Measured alone
 // against the kernel that this one replaced (64 to 1024 threads of up to nine

@@ -18,12 +18,12 @@
 // so each candidate costs O(M log d).  Bounds on E between a few hundred
 // marks leave a short range of a, and its breakpoints (of all d M) are spread
 // over the threads; the smallest error wins, ties to the smallest g
-// (paper_search).
+// (paper_search.hpp).
 // Bound by the latency of the searches (one wavefront per SIMD where channels
 // are few): levels are searched side by side, most breakpoints not at all.
 // 128 channels of 1152 weights, 4 bits, two points: 1984 us with every
 // breakpoint's three grid points and vertices searched level by level, 509 us
-// with the marks and searches side by side, 293 us with one search per
+// with the marks and searches side by side, 299 us with one search per
 // breakpoint left (vertices outside their piece and the grid points below a
 // breakpoint that its error rules out skipped).
 //
