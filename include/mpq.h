@@ -138,9 +138,9 @@ int64_t mpq_fit_max_dim(int n_grid);
  * to fp32; each fp32 product is summed on the 16-bit matrix cores, with fp32
  * accumulation, from four products of fp16 pieces of the scaled operands
  * (d >= 128, c_out >= 256, or 384 where d n > 3 2^20, and rows of X whose root
- * mean squares are at least 2^-10 of X's largest magnitude: three pieces of
- * w - w~, exact to 2^-39 of its largest, and two of X, within 2^-23), or else
- * from six products of exact three-piece bf16 splits;
+ * mean squares are at least 2^-10 of the power of two at or below X's largest
+ * magnitude: three pieces of w - w~, exact to 2^-39 of its largest, and two of
+ * X, within 2^-23), or else from six products of exact three-piece bf16 splits;
  * the sum over the batch is fp64.
  *
  * Arguments

@@ -85,7 +85,7 @@ constexpr int kMinSlabs = 4;      // shortest K range (slabs) of a listed layer'
 constexpr int kThreads = 512;   // GEMM workgroup: four wavefronts multiply (64 x 64 of the tile each), four stage
 constexpr int kStageT = 256;    // threads of the staging wavefronts
 constexpr int kPieces = 3;      // pieces of an fp32 operand (of X with fp16: two)
-constexpr int kSpread = 10;     // fp16 pieces: a row of X has a root mean square of 2^-kSpread of X's largest value or more
+constexpr int kSpread = 10;     // fp16 pieces: a row of X has a root mean square of 2^(ex - kSpread) or more, ex the exponent of X's largest value
 constexpr int kMinExpX = -50;   // and that value an exponent of this or more
 constexpr int kHalfMinD = 128;  // fp16 pieces: shortest rows
 constexpr int kHalfMinC = 256;  // and fewest channels,
@@ -545,10 +545,11 @@ __device__ __forceinline__ _Float16 *piece_at(uint16_t *tiles, int buf, int piec
 // would be the same in all, hence its third piece.  The last (only elements
 // below 2^-15 of their row's maximum lose anything) must not count against
 // the row's output, so the feature that meets the maximum has to be there:
-// every row of X must have a root mean square of 2^-kSpread of X's largest
-// value or more.  Then the row's largest product alone has a root mean square
-// of 2^-kSpread |D|max |X|max, and what d elements lose, 2^-40 |D|max each at
-// random, is 2^-30 sqrt(d) of that at most.  (A rule on the rows' maxima, with
+// every row of X must have a mean square of 2^(2 (ex - kSpread)) or more, ex the
+// exponent of X's largest value.  Then the row's largest product alone has a
+// root mean square of 2^(ex - kSpread) |D|max, and what d elements lose, 2^-40
+// |D|max each at random times X below 2^(ex + 1), is 2^-29 sqrt(d) of that at
+// most.  (A rule on the rows' maxima, with
 // zero rows left out, let a large weight on a feature that is dead or hardly
 // ever nonzero hide weights 2^-28 of it, 4e-5 off.)  A third fewer fp32
 // additions round off less.  A row of X with less, a non-finite X or one near

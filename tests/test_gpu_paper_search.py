@@ -74,3 +74,17 @@ def test_grid_points_on_breakpoints(orc, bits):
     W[6:] = rng.integers(16, 20, (6, d)) / np.float32(16)
     W[:, d // 2] = np.float32([12, 16, 25] * 4)
     _ok(orc.verify_paper(W, bits, 2, 0.0, *_fit_paper(W, bits, 2, 0.0, 2.0 ** -10)))
+
+
+def test_long_channels_at_the_largest_code(orc):
+    """The same on the kernel for long channels (their sorted magnitudes in global memory)."""
+    say("case paper search, saturated, d=8300")
+    rng = np.random.default_rng(60)
+    d = 8300
+    W = np.empty((2, d), dtype=np.float32)
+    W[0] = rng.choice([-1.0, 1.0], d)
+    W[1] = np.float32(0.05) * (1 + np.float32(0.05) * rng.standard_normal(d).astype(np.float32))
+    W[:, 11] = np.float32(40.0) * np.abs(W).max(1)
+    out = _fit_paper(W, 2, 1, 0.0, 2.0 ** -10)
+    assert (out[2] == 1).all() and (out[1][:, 0] < 2 * np.abs(W[:, 0])).all()
+    _ok(orc.verify_paper(W, 2, 1, 0.0, *out))
