@@ -1,7 +1,7 @@
 """The output error on both sides of the rule that chooses the GEMM's operand
 pieces (layers of at least 256 rows, 384 for a large X, of at least 128, and an X whose features' root mean squares lie within 2^10
-of its largest value, take fp16 ones): ranges within, just past and far past it, a row of X of
-zeros, tiny and huge scales, and non-finite values; formed rows (with the reference error), rows the
+of its largest value, take fp16 ones): ranges within, just past and far past it, with a row of X of
+zeros (bf16 ones) and without, tiny and huge scales, and non-finite values; formed rows (with the reference error), rows the
 fit wrote, and a calibration fit's listed rows."""
 import numpy as np
 import pytest
@@ -235,3 +235,20 @@ def test_channels_where_the_pieces_change(orc, C, d, n):
     eo, ro = _oracle_err(orc, W, out, X)
     eg, rg = _gpu_err(W, out, X)
     assert np.all(np.abs(eg - eo) <= 1e-5 * eo) and np.all(np.abs(rg - ro) <= 1e-5 * ro)
+
+
+@pytest.mark.parametrize("C,d,n", [(256, 129, 7), (300, 128, 200), (257, 1600, 130), (260, 2047, 33)])
+@pytest.mark.parametrize("spread,xs,ws", [(0, 0, 0), (9, 0, 0), (10, 0, 0), (9, -49, 20), (9, -52, 20), (8, 60, -70)])
+def test_against_oracle_without_dead_features(orc, C, d, n, spread, xs, ws):
+    """The smallest feature's root mean square on both sides of 2^-10 of X's largest value (0.7 to 0.8 of its own
+    largest one, 2^-spread), that value on both sides of 2^-50, and a large X with small weights."""
+    say(f"case pieces, every feature alive, C={C} d={d} n={n} spread={spread} xs={xs} ws={ws}")
+    W, X = _rows(C, d, n, spread, 3 * C + d)
+    W = (W * np.float32(2.0 ** ws)).astype(np.float32)
+    X = (X * np.float32(2.0 ** xs)).astype(np.float32)
+    out = gpu_fit(W, 4, 3, 64, 1e-3)
+    eo, ro = _oracle_err(orc, W, out, X)
+    eg, rg = _gpu_err(W, out, X)
+    for g, o in ((eg, eo), (rg, ro)):
+        ok = (o > 1e-36) & (o < 1e38)
+        assert np.all(np.abs(g - o)[ok] <= 1e-5 * o[ok]), np.max(np.abs(g - o)[ok] / o[ok])

@@ -80,3 +80,17 @@ def test_caller_grid_at_the_table_entries(orc, C, d, bits, G):
         say(f"case table grid {k} C={C} d={d} bits={bits} G={grid.size}")
         out = gpu_fit(W, bits, 3, grid.size, 1e-4, grid=grid)
         assert_parity(orc, W, bits, 3, grid.size, 1e-4, out, grid=grid)
+
+
+@pytest.mark.parametrize("d", [257, 512, 769, 1280])
+def test_few_and_many_channels_agree_on_a_caller_grid(d):
+    """On a caller's grid up to 1024 channels of one wavefront count as few: the same bits on both sides."""
+    rng = np.random.default_rng(7 * d)
+    rows = np.concatenate([_lattice_rows(d, rng), rng.standard_normal((1030, d)).astype(np.float32)])
+    geo = np.exp(np.linspace(np.log(0.05), 0.0, 130)).astype(np.float32)
+    for bits, tol in ((4, 1e-4), (2, 1e-2), (8, 1e-7)):
+        say(f"case few/many on a caller's grid d={d} bits={bits}")
+        few = gpu_fit(np.ascontiguousarray(rows[:1024]), bits, 3, geo.size, tol, grid=geo)
+        many = gpu_fit(np.ascontiguousarray(rows), bits, 3, geo.size, tol, grid=geo)
+        for a, b in zip(few, many):
+            assert np.array_equal(a, b[:1024])
